@@ -80,6 +80,7 @@ struct PrefillArgs {
   KvAddr kv;
   int32_t h_q, h_kv, m;
   float scale;
+  int32_t by_length;       // sparse: rows of a band run longest list first
   Batch batch;
 };
 
@@ -271,6 +272,57 @@ struct Shape {
   static constexpr int WAVES = HALF ? M : 2 * M;
 };
 
+// Order of a sparse launch's rows (PrefillArgs::by_length).  With KV head and
+// blockIdx both taken modulo 8, an XCD works on one KV head: about 32 rows at a
+// time, all walking their lists up from tile 0.  Their common tiles are read
+// from L2 only while the rows stay within its 4 MB of each other (128 tiles
+// at C = 128).  In q-tile order they do not: list lengths vary by some 7 %
+// between neighbouring rows, so after a few rows the workgroups of an XCD
+// stand at unrelated places.  Taking the rows of every band of 64 q-tiles
+// longest list first keeps them in step (the next 32 rows are of nearly one
+// length, so they start and end together): the 128K 32/8-head layer (rho 0.1)
+// hits L2 on 66 % of its requests instead of 22 % and runs in 22.9 ms a pass
+// instead of 23.8, 32K 1.286 instead of 1.315 ms, 64K with C = 256 4.53
+// instead of 4.70 ms (one box, both sides alternating).
+//
+// Each wave finds its row by itself, without a workspace: lane l of the band
+// reads the list bounds of its l-th row, and the idx-th longest (equal
+// lengths in q-tile order) is selected by the bits of the lengths, from the
+// top.  The 12 highest bits a length of this request can have take part;
+// they order rows of up to 4095 tiles exactly and longer ones to within the
+// dropped bits, and any lengths (malformed lists too) give a permutation.
+struct RowPick {
+  int qt, list_begin, n_tiles;
+};
+__device__ __forceinline__ RowPick pick_row(const int32_t* row_ptr, int row0, int t_q, int t_kv,
+                                            int idx, int lane) {
+  const int top = t_q - (idx & ~63);        // one past the band's last q-tile
+  const int nb = min(top, 64);              // rows of the band: lane l has q-tile top - 1 - l
+  const int r = row0 + top - 1 - min(lane, nb - 1);
+  const int beg = row_ptr[r];
+  const uint32_t len = (uint32_t)(row_ptr[r + 1] - beg);
+  constexpr int BITS = 12;
+  const int shift = max(0, 32 - __builtin_clz((uint32_t)t_kv) - BITS);
+  uint64_t set[BITS];
+#pragma unroll
+  for (int j = 0; j < BITS; ++j) set[j] = __builtin_amdgcn_ballot_w64((len >> (shift + j)) & 1u);
+  uint64_t in = __builtin_amdgcn_ballot_w64(lane < nb);
+  int k = idx & 63;
+#pragma unroll
+  for (int j = BITS - 1; j >= 0; --j) {
+    const uint64_t one = set[j] & in;
+    const int n = __builtin_popcountll(one);
+    in = k < n ? one : in & ~set[j];
+    k = k < n ? k : k - n;
+  }
+  // the k-th lane left
+  const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0));
+  const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(before == k) & in);
+  return {top - 1 - l, __builtin_amdgcn_readlane(beg, l),
+          __builtin_amdgcn_readlane((int)len, l)};
+}
+
 template <int C, int M, bool DENSE, bool PAGED>
 __global__ void __launch_bounds__(64 * (Shape<C, M>::WAVES))
 prefill_kernel(PrefillArgs a) {
@@ -302,14 +354,20 @@ prefill_kernel(PrefillArgs a) {
   const int local = w - Rd.work_begin;
   const int h = local % a.h_kv;
   const int rank = local / a.h_kv;
-  const int qt = t_q - 1 - (HALF ? rank >> 1 : rank);
-  const int row = Rd.row_base + h * t_q + qt;
+  int qt = t_q - 1 - (HALF ? rank >> 1 : rank);
   const int n_c = n_kv - n_q;
 
   int list_begin = 0, n_tiles;
   if (DENSE) {
     n_tiles = min(n_c + (qt + 1) * TILE - 1, n_kv - 1) / TILE + 1;
+  } else if (a.by_length) {
+    const RowPick rp = pick_row(a.row_ptr, Rd.row_base + h * t_q, t_q, t_kv,
+                                HALF ? rank >> 1 : rank, lane);
+    qt = rp.qt;
+    list_begin = rp.list_begin;
+    n_tiles = rp.n_tiles;
   } else {
+    const int row = Rd.row_base + h * t_q + qt;
     list_begin = uniform_load(a.row_ptr, row);
     n_tiles = uniform_load(a.row_ptr, row + 1) - list_begin;
   }
@@ -1155,13 +1213,18 @@ __global__ void __launch_bounds__(64 * M * q16_blocks(M)) prefill_q16_kernel(Pre
   const int local = w - Rd.work_begin;
   const int h = local % a.h_kv;
   const int rank = local / a.h_kv;
-  const int qt = t_q - 1 - rank / PARTS;
-  const int row = Rd.row_base + h * t_q + qt;
+  int qt = t_q - 1 - rank / PARTS;
   const int n_c = n_kv - n_q;
   int list_begin = 0, n_tiles;
   if (DENSE) {
     n_tiles = min(n_c + (qt + 1) * TILE - 1, n_kv - 1) / TILE + 1;
+  } else if (a.by_length) {
+    const RowPick rp = pick_row(a.row_ptr, Rd.row_base + h * t_q, t_q, t_kv, rank / PARTS, lane);
+    qt = rp.qt;
+    list_begin = rp.list_begin;
+    n_tiles = rp.n_tiles;
   } else {
+    const int row = Rd.row_base + h * t_q + qt;
     list_begin = uniform_load(a.row_ptr, row);
     n_tiles = uniform_load(a.row_ptr, row + 1) - list_begin;
   }
@@ -1695,6 +1758,20 @@ hipError_t launch_c(const PrefillArgs& a, bool dense, int n_work, hipStream_t s)
 
 }  // namespace
 
+// Whether a sparse launch runs the rows of a band longest list first: when
+// there are rounds of work items to order (at least two per CU), and what it
+// costs (the first loads of a row wait for its band's list bounds, about 0.5
+// us) is either hidden by the other workgroups of the CU (GQA 1 and 2 at C
+// <= 128: 103 us instead of 106 for 16K tokens of GQA 1 at C = 64, 221
+// instead of 225 us for four 4K prompts of GQA 2) or paid for by K/V that do
+// not fit an XCD's L2: over 8 MB of one KV head (9K tokens, 4.6 MB: 252 us
+// in this order, 246 in q-tile order; 32K, 16 MB: 1.286 and 1.315 ms).
+static bool rows_by_length(int head_dim, int m, int n_work, int t_kv_longest) {
+  if (n_work < 512) return false;
+  if (head_dim <= 128 && m <= 2) return true;
+  return (int64_t)t_kv_longest * TILE * head_dim * 4 > (8 << 20);
+}
+
 hipError_t launch_prefill(const PrefillLaunch& L, hipStream_t stream) {
   PrefillArgs a;
   a.q = static_cast<const bf16_t*>(L.q);
@@ -1725,6 +1802,7 @@ hipError_t launch_prefill(const PrefillLaunch& L, hipStream_t stream) {
       n_work += per_row * a.h_kv * a.batch.r[i].t_q;
     }
     if (n_work == 0) continue;
+    a.by_length = !dense && rows_by_length(L.head_dim, a.m, n_work, a.batch.r[0].t_kv);
     hipError_t e;
     switch (L.head_dim) {
       case 64: e = launch_c<64>(a, dense, n_work, stream); break;

@@ -1,0 +1,56 @@
+"""Row order of the sparse prefill: a launch large enough to take the rows of a
+band longest list first writes, bit for bit, what the same rows give in
+launches too small for it (one KV head at a time)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_12193_amd import bfla
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(rng, h_kv, t_q, t_kv, n_c_tiles):
+    """Random ascending lists: empty rows, full rows, equal lengths in runs."""
+    rows = []
+    for h in range(h_kv):
+        for qt in range(t_q):
+            causal = n_c_tiles + qt + 1
+            kind = rng.integers(0, 8)
+            n = 0 if kind == 0 else min(causal, 5) if kind < 4 else int(rng.integers(1, min(causal, 24) + 1))
+            rows.append(np.sort(rng.choice(causal, size=n, replace=False)).astype(np.int32))
+    ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    return ptr, np.concatenate(rows + [np.zeros(1, np.int32)])
+
+
+# (head dim, GQA, KV heads, query tiles, prefix tiles): two workgroups or more
+# per CU; over 8 MB of K/V with one workgroup per row, half-tile rows, and the
+# quarter-tile rows of head dim 256; tiles that leave a short last band
+@pytest.mark.parametrize("c,m,h_kv,t_q,pre", [(64, 1, 4, 130, 0), (128, 2, 8, 65, 3),
+                                              (128, 4, 4, 129, 140), (128, 5, 4, 67, 200),
+                                              (256, 2, 4, 128, 10), (256, 5, 2, 65, 70)])
+def test_rows_by_length_equal_rows_in_order(c, m, h_kv, t_q, pre):
+    rng = np.random.default_rng(c + m)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    n_q, n_kv = 64 * t_q - 5, 64 * (t_q + pre) - 5
+    q, k, v = (torch.randn(h, n, c, device="cuda", generator=gen).to(torch.bfloat16)
+               for h, n in ((m * h_kv, n_q), (h_kv, n_kv), (h_kv, n_kv)))
+    ptr, cols = _lists(rng, h_kv, t_q, t_q + pre, pre)
+    dptr, dcols = torch.from_numpy(ptr).cuda(), torch.from_numpy(cols).cuda()
+    prm = bfla.params()
+
+    def run(heads, rp):
+        prob = bfla.Problem([n_q], [n_kv], m * len(heads), len(heads), c)
+        qs = q[m * heads[0]:m * (heads[-1] + 1)]
+        o = torch.full_like(qs, float("nan"))
+        lse = torch.full((m * len(heads) * n_q,), float("nan"), device="cuda")
+        kv = bfla.KV(k[heads[0]:heads[-1] + 1], v[heads[0]:heads[-1] + 1])
+        bfla.bfla_sparse_prefill(prob, prm, bfla.view_hnc(qs), kv, rp, dcols, bfla.view_hnc(o), lse)
+        torch.cuda.synchronize()
+        return o, lse.view(-1, n_q)
+
+    o, lse = run(list(range(h_kv)), dptr)
+    for h in range(h_kv):
+        oh, lh = run([h], dptr[h * t_q:(h + 1) * t_q + 1].contiguous())
+        assert torch.equal(o[m * h:m * (h + 1)], oh)
+        assert torch.equal(lse[m * h:m * (h + 1)], lh)
