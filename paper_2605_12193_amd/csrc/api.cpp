@@ -257,7 +257,7 @@ Stage1Layout stage1_layout(const bfla_problem* prob, const bfla_params* pr) {
   for (int g0 = 0; g0 < prob->batch; g0 += kLaunchRequests) {
     const int n = std::min(kLaunchRequests, prob->batch - g0);
     const EstimatePlan plan = estimate_plan(prob->n_q + g0, prob->n_kv + g0, n, prob->h_q,
-                                            prob->head_dim, pr->block, pr->group);
+                                            prob->h_kv, prob->head_dim, pr->block, pr->group);
     lay.splits.push_back(plan.split);
     lay.partial_bytes = std::max(lay.partial_bytes, plan.partial_bytes);
   }

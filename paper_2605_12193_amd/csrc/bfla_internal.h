@@ -18,9 +18,42 @@ constexpr int kScoreTileM = 256;
 constexpr int kScoreTileN = 128;
 constexpr int kScoreChunk = 64;
 constexpr int kScorePagesMax = 2056;
+// row units: query groups of one head; kScoreUnits of them per tile
+constexpr int kScoreUnit = 32;
+constexpr int kScoreUnits = kScoreTileM / kScoreUnit;
 // stages per inner accumulation chain of the score GEMM (summed into a
 // second accumulator; a split of the inner dimension cuts between chains)
 constexpr int kScoreChain = 8;
+
+// Score tiles of one request and KV head.  A row unit is kScoreUnit query
+// groups of one head: unit u holds group block u / m of head u % m.  A row tile
+// is kScoreUnits consecutive units, so it covers the m heads that share its
+// keys over few query groups (a causal edge of 256 / m groups).  Tiles are
+// numbered in bands of up to 4 row tiles (fastest), then columns, then the next
+// band: with the KV head fastest of all (an XCD works on one head), the 32
+// tiles that run together on an XCD cover about 4 x 8 row and column tiles,
+// the shape that shares most of its Q and K in L2.  (Runs of 2, 4 or 8 group
+// blocks of one head in a tile: within 2 % at 32K, 64K and 128K.)
+struct ScoreGrid {
+  int nqg, nkg;   // query / key groups
+  int nu;         // row units
+  int nrt, nct;   // row / column tiles
+  __host__ __device__ __forceinline__ ScoreGrid(int n_q, int n_kv, int g, int m)
+      : nqg((n_q + g - 1) / g), nkg((n_kv + g - 1) / g),
+        nu(m * ((nqg + kScoreUnit - 1) / kScoreUnit)),
+        nrt((nu + kScoreUnits - 1) / kScoreUnits), nct((nkg + kScoreTileN - 1) / kScoreTileN) {}
+  __host__ __device__ __forceinline__ int tiles() const { return nrt * nct; }
+  __device__ __forceinline__ void locate(int t, int& rt, int& ct) const {
+    const int band = 4 * nct, r0 = t / band * 4, in = t - r0 * nct;
+    const int w = nrt - r0 < 4 ? nrt - r0 : 4;
+    ct = in / w;
+    rt = r0 + in - ct * w;
+  }
+  __device__ __forceinline__ int index(int rt, int ct) const {
+    const int r0 = rt & ~3, w = nrt - r0 < 4 ? nrt - r0 : 4;
+    return r0 * nct + ct * w + (rt - r0);
+  }
+};
 
 // How Stage 1 runs a problem: score tiles in the launch (all, and those
 // holding a causal block pair), the split of the inner dimension (1: none;
@@ -35,7 +68,7 @@ struct EstimatePlan {
   size_t partial_bytes;
 };
 EstimatePlan estimate_plan(const int32_t* n_q, const int32_t* n_kv, int batch, int h_q,
-                           int head_dim, int block, int group);
+                           int h_kv, int head_dim, int block, int group);
 
 struct PrefillLaunch {
   const void* q;

@@ -6,24 +6,30 @@
 // is a GEMM whose rows are flattened g-token query groups and whose columns
 // are flattened key groups (inner dimension g*C; a flattened group of a
 // row-major [N][C] head is g consecutive token rows, so no copy is made,
-// eq6-eq7).  256 x 128 output tiles, 8 waves of 32 x 128, bf16 MFMA
-// 32x32x16; Q/K chunks of 64 inner elements go from buffer loads straight
-// into a 3-slot LDS ring (two chunks in flight, one workgroup per CU);
-// only tiles holding a causal block pair are computed (eq11-eq14).  The
-// epilogue max-pools each G x G group block into the block score (eq10)
-// and stores it as float.  Accumulation is two-level: chains of 32 MFMA
-// steps (512 products) are summed into a second float accumulator, which
-// keeps the score error well inside the near-tie band of the selection.
+// eq6-eq7).  The rows of one KV head come in units of 32 consecutive groups
+// of one query head, ordered group block first and head of the GQA group
+// second, and an output tile is 8 such units x 128 key groups: a short prompt
+// fills a tile with the m heads that share its keys, and the causal edge of
+// a tile is 256 / m groups wide instead of 256.  8 waves of 64 x 64, bf16
+// MFMA 32x32x16; Q/K chunks of 64 inner elements go from buffer loads
+// straight into a 3-slot LDS ring (two chunks in flight, one workgroup per
+// CU); only tiles holding a causal block pair are computed (eq11-eq14), and
+// waves without one only load.  The epilogue max-pools each G x G group
+// block into the block score (eq10) and stores it as float.  Accumulation is
+// two-level: chains of 32 MFMA steps (512 products) are summed into a second
+// float accumulator, which keeps the score error well inside the near-tie
+// band of the selection.
 // When a problem has too few tiles to fill the chip (a split S > 1 from
 // estimate_plan), each tile runs as S workgroups over consecutive runs of
-// whole chains that store their raw group sums; pool_kernel adds the S sums
-// in part order, then pools and stores as the epilogue would.
+// whole chains that store their raw group sums; the selection then adds the
+// S sums in part order and pools them as the epilogue would.
 //
 // Kernel 2 (select): one workgroup per (request, KV head, query block),
 // one wave per query head of the group: block softmax over the causal KV
 // blocks (eq15), keep-mass selection by repeated arg-max in the order
 // (score descending, block index ascending) with a sequential float
 // running mass (eq16-eq18), then OR of the m heads into the u8 mask row.
+// After a split score GEMM it pools the block scores itself first.
 // On request each wave also stores its own head's keep set (eq18).
 #include <algorithm>
 
@@ -36,12 +42,12 @@ namespace {
 constexpr int BM = kScoreTileM;   // query groups per tile (32 per wave)
 constexpr int BN = kScoreTileN;   // key groups per tile
 constexpr int BK = kScoreChunk;   // inner elements per stage
-// 8 waves (two per SIMD): each keeps its own DMA loads in flight, and the
-// kernel is bound by the memory requests in flight (4 waves of 64 x 128
-// outputs each were 12 % slower)
+// 8 waves (two per SIMD), 64 x 64 outputs each: four LDS fragments feed four
+// MFMAs (32 x 128 outputs read five)
 constexpr int NW = 8;
 constexpr int NT = 64 * NW;
-constexpr int XB = BM / NW / 32;   // 32-row MFMA blocks per wave
+constexpr int UNIT = kScoreUnit;   // query groups of one head per row unit
+constexpr int UNITS = BM / UNIT;   // units per tile
 constexpr int CHAIN = kScoreChain;  // stages per inner accumulation chain (32 MFMA k-steps)
 constexpr int MAX_LKV = 65536;
 
@@ -61,12 +67,17 @@ struct ScoreArgs {
 };
 
 struct SelectArgs {
-  const float* scores;
+  float* scores;
   float* dbg;        // non-null: also fill non-causal entries with -inf
   uint8_t* block_mask;
   uint8_t* head_mask;  // non-null: per-query-head keep sets, score layout
   int32_t h_q, h_kv, m, b;
   float gamma, alpha;
+  // after a split score GEMM: its raw group sums, which this kernel pools
+  const float* partials;
+  int32_t split, g;
+  int64_t part_stride;                   // floats between the parts of a tile
+  int32_t tile_begin[kLaunchRequests];   // first score tile of each request
   Batch batch;       // work_begin = first (h, i) row of request r
 };
 
@@ -77,9 +88,6 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 __device__ __forceinline__ uint4 ld16(const bf16_t* p) {
   return *reinterpret_cast<const uint4*>(p);
 }
-
-__host__ __device__ __forceinline__ int row_tiles(int groups) { return (groups + BM - 1) / BM; }
-__host__ __device__ __forceinline__ int col_tiles(int groups) { return (groups + BN - 1) / BN; }
 
 // One ring stage: the Q tile (BM rows) and the K tile (BN rows) of 64 bf16
 // each (128 B per row, no padding).  Rows are XOR-swizzled in 16-byte chunks
@@ -135,8 +143,7 @@ __global__ void __launch_bounds__(NT, 1) scores_kernel(ScoreArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
 
-  // ---- tile decode: (split part, request, tile rank, head) with the KV
-  // head fastest and the part slowest ----
+  // ---- tile decode: (split part, request, tile, KV head), head fastest ----
   const int part = blockIdx.x / a.total_tiles;
   const int tile_id = blockIdx.x - part * a.total_tiles;
   const int ri = find_req(a.batch, tile_id);
@@ -145,43 +152,53 @@ __global__ void __launch_bounds__(NT, 1) scores_kernel(ScoreArgs a) {
   const int64_t q_off = R.q_off, kv_off = R.kv_off;
   const int bt_row = R.bt_row;
   const int local = tile_id - R.work_begin;
-  const int nqg = (n_q + a.g - 1) / a.g;    // query groups
-  const int nkg = (n_kv + a.g - 1) / a.g;   // key groups
-  const int ntj = col_tiles(nkg);
+  const ScoreGrid tg(n_q, n_kv, a.g, a.m);
+  const int nqg = tg.nqg, nkg = tg.nkg;
   const int h = local % a.h_kv;
-  const int pm = (local / a.h_kv) % a.m;
-  const int rank = local / a.h_q;
-  const int ti = rank / ntj, tj = rank % ntj;
-  const int p = h * a.m + pm;
+  int rt, ct;
+  tg.locate(local / a.h_kv, rt, ct);
   const int n_c = n_kv - n_q;
 
-  // skip tiles without any causal block pair
-  {
-    int gi_last = min(nqg, (ti + 1) * BM) - 1;
-    int i_max = gi_last / G;
-    int e_i = min(n_c + (i_max + 1) * a.b - 1, n_kv - 1);
-    int j_min = (tj * BN) / G;
-    if (j_min * a.b > e_i) return;
-  }
+  // last key position of the query block that holds the last group of a
+  // group block
+  auto block_end = [&](int blk) __attribute__((always_inline)) {
+    const int i_max = (min(nqg, (blk + 1) * UNIT) - 1) / G;
+    return min(n_c + (i_max + 1) * a.b - 1, n_kv - 1);
+  };
+  const int j_min = (ct * BN) / G;   // first KV block of the tile
+  const int e_tile = block_end((min(tg.nu, (rt + 1) * UNITS) - 1) / a.m);
+  if (j_min * a.b > e_tile) return;  // no causal block pair
 
   // ---- direct global -> LDS loads through buffer descriptors ----
   // Wave w, load i fills rows [8 (NW i + w), +8) of the Q (i < A_LOADS) or K
   // (i < B_LOADS) tile: lane l writes LDS chunk l % 8 of row 8 (NW i + w) +
-  // l / 8 and fetches the logical chunk that the swizzle places there.  Out-of-range offsets
-  // (padding groups, tokens past the end, bad pages) read as zeros.  The Q
-  // descriptor starts at the tile's first query token, so it spans at most
-  // BM * g token rows.
-  const int q_tok0 = ti * BM * a.g;
-  const int q_tile_tok = min(n_q - q_tok0, BM * a.g);
-  const i32x4 qrs =
-      make_rsrc(a.q + q_off + (int64_t)p * a.q_sh + (int64_t)q_tok0 * a.q_st,
-                (uint32_t)(((int64_t)(q_tile_tok - 1) * a.q_st + a.C) * 2));
+  // l / 8 and fetches the logical chunk that the swizzle places there.  The 8
+  // Q rows of a load lie in unit 2 i + w / 4, so each load has a descriptor of
+  // its own that spans the unit's tokens (nothing when the unit holds no
+  // causal pair of this tile); row and chunk are the same in all of them.
+  // Out-of-range offsets (padding groups, tokens past the end, bad pages)
+  // read as zeros.
+  const int row_sub = lane >> 3, pch = lane & 7;
+  const int q_row = 8 * (wave & 3) + row_sub;       // group inside the unit
+  const int lch = swz(q_row, pch);                  // the same for the K rows
+  i32x4 qrs[A_LOADS];
+  int q_tok[A_LOADS];                               // tokens of the unit
+#pragma unroll
+  for (int i = 0; i < A_LOADS; ++i) {
+    const int u = rt * UNITS + 2 * i + (wave >> 2);
+    const int uc = min(u, tg.nu - 1), blk = uc / a.m, pm = uc - blk * a.m;
+    const bool live = u < tg.nu && j_min * a.b <= block_end(blk);
+    const int tok0 = blk * UNIT * a.g;
+    q_tok[i] = min(n_q - tok0, UNIT * a.g);
+    qrs[i] = make_rsrc(a.q + q_off + (int64_t)(h * a.m + pm) * a.q_sh + (int64_t)tok0 * a.q_st,
+                       live ? (uint32_t)(((int64_t)(q_tok[i] - 1) * a.q_st + a.C) * 2) : 0u);
+  }
   const i32x4 krs =
       make_rsrc(a.kv.k + (PAGED ? 0 : kv_off) + (int64_t)h * a.kv.stride_head,
                 PAGED ? a.kv.pool_bytes
                       : (uint32_t)(((int64_t)(n_kv - 1) * a.kv.stride_tok + a.C) * 2));
   const int ps_shift = PAGED ? __builtin_ctz(a.kv.page_size) : 0;
-  const int k_tok0 = tj * BN * a.g;                 // first key token of the tile (< n_kv)
+  const int k_tok0 = ct * BN * a.g;                 // first key token of the tile (< n_kv)
   const int first_page = k_tok0 >> ps_shift;
   if (PAGED) {
     // the pages this tile's keys live in, resolved once: byte offset of each
@@ -195,85 +212,102 @@ __global__ void __launch_bounds__(NT, 1) scores_kernel(ScoreArgs a) {
     }
     __syncthreads();
   }
-  const int row_sub = lane >> 3, pch = lane & 7;
-  int q_row_tok[A_LOADS], k_row_tok[B_LOADS];   // first token of each loaded row's group
-  int lch[A_LOADS];                             // logical chunk fetched by this lane
-  bool q_ok[A_LOADS], k_ok[B_LOADS];
+  // Byte offsets at inner element 0; a stage adds one scalar to them.  Rows
+  // without a real group, and key groups past the tile's last causal block,
+  // start at 2^31 and stay out of every range.  A token past the end lies
+  // out of range by itself, unless token rows overlap (stride below C) or a
+  // group spans so much that the offset could wrap; those strides take the
+  // checked form below.
+  const uint32_t q_base = (uint32_t)(((int64_t)q_row * a.g * a.q_st + 8 * lch) * 2);
+  int k_tok[B_LOADS];
+  uint32_t k_base[B_LOADS];
+  bool k_ok[B_LOADS];
 #pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) {
-    const int row = 8 * (NW * i + wave) + row_sub;   // the K rows are the first B_LOADS of these
-    lch[i] = swz(row, pch);
-    q_ok[i] = ti * BM + row < nqg;
-    q_row_tok[i] = row * a.g;   // relative to q_tok0
-    if (i < B_LOADS) {
-      const int gj = tj * BN + row;
-      k_ok[i] = gj < nkg;
-      k_row_tok[i] = gj * a.g;
-    }
+  for (int i = 0; i < B_LOADS; ++i) {
+    const int gj = ct * BN + 8 * (NW * i + wave) + row_sub;
+    k_ok[i] = gj < nkg && (gj / G) * a.b <= e_tile;
+    k_tok[i] = gj * a.g;
+    k_base[i] = !PAGED && k_ok[i] ? (uint32_t)(((int64_t)k_tok[i] * a.kv.stride_tok + 8 * lch) * 2)
+                                  : 0x80000000u;
   }
+  // paged K: the page of a row can change only at multiples of this many
+  // tokens into its group
+  const int page_step = PAGED ? min(a.g & -a.g, a.kv.page_size) : 1;
+  const bool checked = a.q_st < a.C || (!PAGED && (a.kv.stride_tok < a.C ||
+                                                   a.kv.stride_tok * a.g >= (int64_t(1) << 29)));
+  // this workgroup's stages: a run of whole chains (so of whole tokens)
+  const int st_begin = part * a.part_stages;
+  const int st_end = st_begin + a.part_stages;
   const uint32_t ring_lds = LDS_ADDR(&ring[0][0]) + (uint32_t)wave * 1024;
   constexpr uint32_t SLOT_BYTES = (A_ELEMS + B_ELEMS) * 2;
   auto issue = [&](int st) __attribute__((always_inline)) {
     const uint32_t la = ring_lds + (uint32_t)(st % NSTAGE) * SLOT_BYTES;
     const uint32_t lb = la + A_ELEMS * 2;
     const int k0 = st * BK;
-    const int tok_in = k0 / a.C, ch = k0 % a.C;
+    const int tok_in = k0 / a.C, ch = k0 - tok_in * a.C;
+    const uint32_t q_add = (uint32_t)(((int64_t)tok_in * a.q_st + ch) * 2);
+    const uint32_t qo = q_base + q_add;
 #pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) {
-      const int tq = q_row_tok[i] + tok_in;
-      const uint32_t qo = (q_ok[i] && tq < q_tile_tok)
-                              ? (uint32_t)(((int64_t)tq * a.q_st + ch + 8 * lch[i]) * 2)
-                              : 0x80000000u;
-      dma16(qrs, la + i * (NW * 1024), qo);
+    for (int i = 0; i < A_LOADS; ++i)
+      dma16(qrs[i], la + i * (NW * 1024),
+            checked && q_row * a.g + tok_in >= q_tok[i] ? 0x80000000u : qo);
+    if (PAGED) {
+      if (st == st_begin || (ch == 0 && tok_in % page_step == 0)) {
+#pragma unroll
+        for (int i = 0; i < B_LOADS; ++i) {
+          const int tk = k_tok[i] + tok_in;
+          const uint32_t pb = k_ok[i] && tk < n_kv ? page_base[(tk >> ps_shift) - first_page] : BAD_PAGE;
+          k_base[i] = pb;
+        }
+      }
     }
 #pragma unroll
     for (int i = 0; i < B_LOADS; ++i) {
-      const int tk = k_row_tok[i] + tok_in;
-      uint32_t ko = 0x80000000u;
-      if (k_ok[i] && tk < n_kv) {
-        if (PAGED) {
-          const uint32_t pb = page_base[(tk >> ps_shift) - first_page];
-          if (pb != BAD_PAGE)
-            ko = pb + (uint32_t)((((tk & (a.kv.page_size - 1)) * a.kv.stride_tok) + ch +
-                                  8 * lch[i]) * 2);
-        } else {
-          ko = (uint32_t)(((int64_t)tk * a.kv.stride_tok + ch + 8 * lch[i]) * 2);
-        }
+      uint32_t ko;
+      const int tk = k_tok[i] + tok_in;
+      if (PAGED) {
+        const uint32_t in = (uint32_t)(((tk & (a.kv.page_size - 1)) * a.kv.stride_tok + ch + 8 * lch) * 2);
+        ko = k_base[i] != BAD_PAGE && tk < n_kv ? k_base[i] + in : 0x80000000u;
+      } else {
+        ko = k_base[i] + (uint32_t)(((int64_t)tok_in * a.kv.stride_tok + ch) * 2);
+        if (checked && tk >= n_kv) ko = 0x80000000u;
       }
       dma16(krs, lb + i * (NW * 1024), ko);
     }
   };
 
-  // wave w: query-group rows [32 w, +32) x all BN key-group columns
-  f32x16 acc[XB][4], tot[XB][4];
+  // wave w: units 2 (w / 2), + 1 (rows 64 (w / 2) ..) x columns 64 (w % 2) ..
+  const int u0 = rt * UNITS + 2 * (wave >> 1);
+  const int c0w = 64 * (wave & 1);
+  const int j_wave_pos = (ct * BN + c0w) / G * a.b;
+  const bool active = u0 < tg.nu && ct * BN + c0w < nkg &&
+                      j_wave_pos <= block_end(min(u0 + 1, tg.nu - 1) / a.m);
+  f32x16 acc[2][2], tot[2][2];
 #pragma unroll
-  for (int x = 0; x < XB; ++x)
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 4; ++y)
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) { acc[x][y][r] = 0.f; tot[x][y][r] = 0.f; }
 
-  // this workgroup's stages: a run of whole chains
-  const int st_begin = part * a.part_stages;
-  const int st_end = st_begin + a.part_stages;
   auto compute = [&](const bf16_t* A, const bf16_t* B) __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
-      bf16x8 af[XB], bf[4];
+      bf16x8 af[2], bf[2];
 #pragma unroll
-      for (int x = 0; x < XB; ++x) {
-        const int row = (BM / NW) * wave + 32 * x + l32;
+      for (int x = 0; x < 2; ++x) {
+        const int row = 64 * (wave >> 1) + 32 * x + l32;
         af[x] = __builtin_bit_cast(bf16x8, ld16(A + row * BK + 8 * swz(row, 2 * ks + hi)));
       }
 #pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        const int row = 32 * y + l32;
+      for (int y = 0; y < 2; ++y) {
+        const int row = c0w + 32 * y + l32;
         bf[y] = __builtin_bit_cast(bf16x8, ld16(B + row * BK + 8 * swz(row, 2 * ks + hi)));
       }
 #pragma unroll
-      for (int x = 0; x < XB; ++x)
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = mfma32(af[x], bf[y], acc[x][y]);
+        for (int y = 0; y < 2; ++y) acc[x][y] = mfma32(af[x], bf[y], acc[x][y]);
     }
   };
   // s_waitcnt immediates: vmcnt(n) with the other counters left free
@@ -296,44 +330,53 @@ __global__ void __launch_bounds__(NT, 1) scores_kernel(ScoreArgs a) {
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       if (st + NSTAGE - 1 < st_end) issue(st + NSTAGE - 1);
       const int slot = st % NSTAGE;
-      compute(&ring[slot][0], &ring[slot][A_ELEMS]);
+      if (active) compute(&ring[slot][0], &ring[slot][A_ELEMS]);
     }
     // close the chain: fold it into the running total
 #pragma unroll
-    for (int x = 0; x < XB; ++x)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 4; ++y)
+      for (int y = 0; y < 2; ++y)
 #pragma unroll
         for (int r = 0; r < 16; ++r) { tot[x][y][r] += acc[x][y][r]; acc[x][y][r] = 0.f; }
   }
+  if (!active) return;
 
-  // ---- split: store this part's raw group sums (pool_kernel finishes) ----
   // D[row = query group][col = key group]; lane: col l32, rows 8(r/4)+4hi+r%4
+  // ---- split: store this part's raw group sums (the selection pools them) ----
   if (a.split > 1) {
     float* dst = a.partials + (int64_t)blockIdx.x * (BM * BN);
 #pragma unroll
-    for (int x = 0; x < XB; ++x)
+    for (int x = 0; x < 2; ++x) {
+      const int u = u0 + x, gi0 = u / a.m * UNIT;
+      if (u >= tg.nu) break;
 #pragma unroll
-      for (int y = 0; y < 4; ++y)
+      for (int y = 0; y < 2; ++y) {
+        const int col = c0w + 32 * y + l32;
+        if (ct * BN + col >= nkg) continue;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = (BM / NW) * wave + 32 * x + 8 * (r >> 2) + 4 * hi + (r & 3);
-          dst[row * BN + 32 * y + l32] = tot[x][y][r];
+          const int row = 8 * (r >> 2) + 4 * hi + (r & 3);
+          if (gi0 + row < nqg) dst[(64 * (wave >> 1) + 32 * x + row) * BN + col] = tot[x][y][r];
         }
+      }
+    }
     return;
   }
 
   // ---- epilogue: drop padded groups, G x G max pool, causal store ----
-  float* srow_base = a.scores + R.score_off + (int64_t)p * R.l_q * R.l_kv;
 #pragma unroll
-  for (int x = 0; x < XB; ++x) {
+  for (int x = 0; x < 2; ++x) {
+    const int u = u0 + x, blk = u / a.m, p = h * a.m + u - blk * a.m;
+    if (u >= tg.nu) break;
+    float* srow_base = a.scores + R.score_off + (int64_t)p * R.l_q * R.l_kv;
 #pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int gj = tj * BN + 32 * y + l32;
+    for (int y = 0; y < 2; ++y) {
+      const int gj = ct * BN + c0w + 32 * y + l32;
       f32x16 v = tot[x][y];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int gi = ti * BM + (BM / NW) * wave + 32 * x + 8 * (r >> 2) + 4 * hi + (r & 3);
+        const int gi = blk * UNIT + 8 * (r >> 2) + 4 * hi + (r & 3);
         if (gi >= nqg || gj >= nkg) v[r] = -INFINITY;
       }
       // pool over G consecutive query-group rows
@@ -369,92 +412,13 @@ __global__ void __launch_bounds__(NT, 1) scores_kernel(ScoreArgs a) {
       if (j >= R.l_kv) continue;
 #pragma unroll
       for (int r = 0; r < 16; r += (G >= 16 ? 8 : G >= 4 ? 4 : G)) {
-        const int gi = ti * BM + (BM / NW) * wave + 32 * x + 8 * (r >> 2) + 4 * hi + (r & 3);
+        const int gi = blk * UNIT + 8 * (r >> 2) + 4 * hi + (r & 3);
         const int i = gi / G;
         if (i >= R.l_q) continue;
         const int e_i = min(n_c + (i + 1) * a.b - 1, R.n_kv - 1);
         if (j * a.b <= e_i) srow_base[(int64_t)i * R.l_kv + j] = pr[r];
       }
     }
-  }
-}
-
-// Finish of a split score tile, POOL_ROWS group rows per workgroup: the
-// group sums of the `split` parts are added in part order (into LDS), then
-// padded groups are dropped, each G x G group block is max-pooled into its
-// block score (eq10) and the causal blocks are stored (eq11-eq14) -- what
-// the epilogue of an unsplit tile does.
-constexpr int POOL_ROWS = 32;
-constexpr int POOL_THREADS = 256;
-
-template <int G>
-__global__ void __launch_bounds__(POOL_THREADS) pool_kernel(ScoreArgs a) {
-  __shared__ float sum[POOL_ROWS][BN + 4];
-  constexpr int CHUNKS = BM / POOL_ROWS;
-  const int tile_id = blockIdx.x / CHUNKS;
-  const int chunk = blockIdx.x % CHUNKS;
-  const int ri = find_req(a.batch, tile_id);
-  const ReqDesc& R = a.batch.r[ri];
-  const int n_q = R.n_q, n_kv = R.n_kv;
-  const int local = tile_id - R.work_begin;
-  const int nqg = (n_q + a.g - 1) / a.g;
-  const int nkg = (n_kv + a.g - 1) / a.g;
-  const int ntj = col_tiles(nkg);
-  const int h = local % a.h_kv;
-  const int pm = (local / a.h_kv) % a.m;
-  const int rank = local / a.h_q;
-  const int ti = rank / ntj, tj = rank % ntj;
-  const int p = h * a.m + pm;
-  const int n_c = n_kv - n_q;
-  {
-    int gi_last = min(nqg, (ti + 1) * BM) - 1;
-    int i_max = gi_last / G;
-    int e_i = min(n_c + (i_max + 1) * a.b - 1, n_kv - 1);
-    int j_min = (tj * BN) / G;
-    if (j_min * a.b > e_i) return;   // no causal block pair: no part ran
-  }
-  const int row0 = chunk * POOL_ROWS;             // first group row of this chunk
-  if (ti * BM + row0 >= nqg) return;              // only padding rows
-  const int64_t part_stride = (int64_t)a.total_tiles * (BM * BN);
-  const float* src = a.partials + (int64_t)tile_id * (BM * BN) + (int64_t)row0 * BN;
-  // 1. the parts' group sums, in part order, 4 columns per thread
-  for (int e = threadIdx.x; e < POOL_ROWS * (BN / 4); e += POOL_THREADS) {
-    const int r = e / (BN / 4), c4 = e % (BN / 4);
-    const float* s0 = src + r * BN + 4 * c4;
-    float4 v = *reinterpret_cast<const float4*>(s0);
-    for (int q = 1; q < a.split; ++q) {
-      const float4 w = *reinterpret_cast<const float4*>(s0 + q * part_stride);
-      v.x += w.x;
-      v.y += w.y;
-      v.z += w.z;
-      v.w += w.w;
-    }
-    sum[r][4 * c4] = v.x;
-    sum[r][4 * c4 + 1] = v.y;
-    sum[r][4 * c4 + 2] = v.z;
-    sum[r][4 * c4 + 3] = v.w;
-  }
-  __syncthreads();
-  // 2. G x G max pool of real groups, causal store
-  float* srow_base = a.scores + R.score_off + (int64_t)p * R.l_q * R.l_kv;
-  constexpr int PI = POOL_ROWS / G, PJ = BN / G;
-  for (int o = threadIdx.x; o < PI * PJ; o += POOL_THREADS) {
-    const int ii = o / PJ, jj = o % PJ;
-    const int i = (ti * BM + row0) / G + ii, j = tj * PJ + jj;
-    if (i >= R.l_q || j >= R.l_kv) continue;
-    const int e_i = min(n_c + (i + 1) * a.b - 1, n_kv - 1);
-    if (j * a.b > e_i) continue;
-    float best = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      const int gi = ti * BM + row0 + ii * G + u;
-#pragma unroll
-      for (int v = 0; v < G; ++v) {
-        const int gj = tj * BN + jj * G + v;
-        if (gi < nqg && gj < nkg) best = fmaxf(best, sum[ii * G + u][jj * G + v]);
-      }
-    }
-    srow_base[(int64_t)i * R.l_kv + j] = best;
   }
 }
 
@@ -528,6 +492,10 @@ __device__ __forceinline__ void wave_best(float& s, int& j) {
   }
 }
 
+// POOL > 0: the score GEMM was split; POOL = G, and this kernel first adds
+// the parts' group sums in part order, max-pools each G x G group block of
+// its rows (eq10) and stores the block scores.
+template <int POOL>
 __global__ void __launch_bounds__(512) select_kernel(SelectArgs a) {
   __shared__ uint32_t keep_bits[MAX_LKV / 32];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -552,7 +520,46 @@ __global__ void __launch_bounds__(512) select_kernel(SelectArgs a) {
   for (int w = tid; w < words; w += blockDim.x) keep_bits[w] = 0u;
   __syncthreads();
 
-  const float* row = a.scores + R.score_off + ((int64_t)p * R.l_q + i) * R.l_kv;
+  float* const row = a.scores + R.score_off + ((int64_t)p * R.l_q + i) * R.l_kv;
+
+  // Block score (i, j) of this wave's head after a split score GEMM: the max
+  // over the real groups of the G x G block, each the sum of its parts.
+  auto pooled = [&](int j) __attribute__((always_inline)) -> float {
+    constexpr int G = POOL > 0 ? POOL : 1;
+    const ScoreGrid tg(R.n_q, R.n_kv, a.g, a.m);
+    const int u = i * G / UNIT * a.m + wave, ct = j * G / BN;
+    const int64_t tile = a.tile_begin[ri] + (int64_t)tg.index(u / UNITS, ct) * a.h_kv + h;
+    const float* src = a.partials + tile * (BM * BN) +
+                       (u % UNITS * UNIT + i * G % UNIT) * BN + j * G % BN;
+    // PF parts of a row are read before the first is added (one round trip
+    // instead of one per part)
+    constexpr int PF = G <= 2 ? 8 : G <= 4 ? 4 : 2;
+    float best = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < G; ++x) {
+      if (i * G + x >= tg.nqg) break;
+      float v[G];
+      for (int q = 0; q < a.split; q += PF) {
+        float w[PF][G];
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+          for (int y = 0; y < G; ++y)
+            w[f][y] = src[min(q + f, a.split - 1) * a.part_stride + x * BN + y];
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+          for (int y = 0; y < G; ++y)
+            if (q + f < a.split) v[y] = q + f == 0 ? w[f][y] : v[y] + w[f][y];
+      }
+#pragma unroll
+      for (int y = 0; y < G; ++y)
+        if (j * G + y < tg.nkg) best = fmaxf(best, v[y]);
+    }
+    return best;
+  };
+  if (POOL > 0 && (a.gamma >= 1.0f || n_causal > 64 * 16))
+    for (int j = lane; j < n_causal; j += 64) row[j] = pooled(j);
 
   if (a.gamma >= 1.0f) {
     for (int j = tid; j < n_causal; j += blockDim.x) atomicOr(&keep_bits[j >> 5], 1u << (j & 31));
@@ -568,7 +575,15 @@ __global__ void __launch_bounds__(512) select_kernel(SelectArgs a) {
 #pragma unroll
     for (int k = 0; k < ROW_REGS; ++k) {
       const int j = lane + 64 * k;
-      rv[k] = (in_regs && j < n_causal) ? row[j] : -INFINITY;
+      rv[k] = -INFINITY;
+      if (in_regs && j < n_causal) {
+        if (POOL > 0) {
+          rv[k] = pooled(j);
+          row[j] = rv[k];
+        } else {
+          rv[k] = row[j];
+        }
+      }
     }
     // f(j, s) for every causal block j of this lane, in increasing j
     auto for_each = [&](auto&& f) __attribute__((always_inline)) {
@@ -621,16 +636,19 @@ __global__ void __launch_bounds__(512) select_kernel(SelectArgs a) {
 }
 
 template <int G>
-hipError_t launch_scores(const ScoreArgs& a, int n_tiles, hipStream_t s) {
+hipError_t launch_group(const ScoreArgs& a, const SelectArgs& s, int n_tiles, int n_rows,
+                        hipStream_t stream) {
   const dim3 grid((unsigned)((int64_t)n_tiles * a.split));
   if (a.kv.paged)
-    hipLaunchKernelGGL((scores_kernel<G, true>), grid, dim3(NT), 0, s, a);
+    hipLaunchKernelGGL((scores_kernel<G, true>), grid, dim3(NT), 0, stream, a);
   else
-    hipLaunchKernelGGL((scores_kernel<G, false>), grid, dim3(NT), 0, s, a);
+    hipLaunchKernelGGL((scores_kernel<G, false>), grid, dim3(NT), 0, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.split == 1) return e;
-  hipLaunchKernelGGL((pool_kernel<G>), dim3((unsigned)n_tiles * (BM / POOL_ROWS)),
-                     dim3(POOL_THREADS), 0, s, a);
+  if (e != hipSuccess) return e;
+  if (a.split > 1)
+    hipLaunchKernelGGL((select_kernel<G>), dim3(n_rows), dim3(64 * a.m), 0, stream, s);
+  else
+    hipLaunchKernelGGL((select_kernel<0>), dim3(n_rows), dim3(64 * a.m), 0, stream, s);
   return hipGetLastError();
 }
 
@@ -668,7 +686,7 @@ hipError_t launch_estimate(const EstimateLaunch& L, hipStream_t stream) {
   s.gamma = L.gamma;
   s.alpha = L.alpha;
 
-  // scores (and their pooling when split) then the selection, once per group
+  // scores then the selection (which pools split scores), once per group
   // of kLaunchRequests requests; the groups share the partial-sum buffer in
   // stream order
   const size_t n_groups = (L.reqs.size() + kLaunchRequests - 1) / kLaunchRequests;
@@ -683,25 +701,18 @@ hipError_t launch_estimate(const EstimateLaunch& L, hipStream_t stream) {
       d = L.reqs[g0 + r];
       if (d.l_kv > MAX_LKV) return hipErrorInvalidValue;
       d.work_begin = n_tiles;
-      const int nqg = (d.n_q + a.g - 1) / a.g, nkg = (d.n_kv + a.g - 1) / a.g;
-      n_tiles += a.h_q * row_tiles(nqg) * col_tiles(nkg);
+      s.tile_begin[r] = n_tiles;
+      n_tiles += a.h_kv * ScoreGrid(d.n_q, d.n_kv, a.g, m).tiles();
     }
     a.split = L.splits[gi];
     a.total_tiles = n_tiles;
     if (a.split < 1 || (a.split > 1 && (n_stage % (a.split * CHAIN) != 0 || !a.partials)))
       return hipErrorInvalidValue;
     a.part_stages = n_stage / a.split;
-    hipError_t e;
-    switch (a.G) {
-      case 1: e = launch_scores<1>(a, n_tiles, stream); break;
-      case 2: e = launch_scores<2>(a, n_tiles, stream); break;
-      case 4: e = launch_scores<4>(a, n_tiles, stream); break;
-      case 8: e = launch_scores<8>(a, n_tiles, stream); break;
-      case 16: e = launch_scores<16>(a, n_tiles, stream); break;
-      default: return hipErrorInvalidValue;
-    }
-    if (e != hipSuccess) return e;
-
+    s.partials = a.partials;
+    s.split = a.split;
+    s.g = a.g;
+    s.part_stride = (int64_t)n_tiles * (BM * BN);
     s.batch.n_req = n;
     int n_rows = 0;
     for (int r = 0; r < n; ++r) {
@@ -709,8 +720,15 @@ hipError_t launch_estimate(const EstimateLaunch& L, hipStream_t stream) {
       s.batch.r[r].work_begin = n_rows;
       n_rows += L.h_kv * s.batch.r[r].l_q;
     }
-    hipLaunchKernelGGL(select_kernel, dim3(n_rows), dim3(64 * m), 0, stream, s);
-    e = hipGetLastError();
+    hipError_t e;
+    switch (a.G) {
+      case 1: e = launch_group<1>(a, s, n_tiles, n_rows, stream); break;
+      case 2: e = launch_group<2>(a, s, n_tiles, n_rows, stream); break;
+      case 4: e = launch_group<4>(a, s, n_tiles, n_rows, stream); break;
+      case 8: e = launch_group<8>(a, s, n_tiles, n_rows, stream); break;
+      case 16: e = launch_group<16>(a, s, n_tiles, n_rows, stream); break;
+      default: return hipErrorInvalidValue;
+    }
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -30,52 +30,62 @@ bool estimate_pages_fit(int group, int page_size) {
 }
 
 EstimatePlan estimate_plan(const int32_t* n_q, const int32_t* n_kv, int batch, int h_q,
-                           int head_dim, int block, int group) {
+                           int h_kv, int head_dim, int block, int group) {
   EstimatePlan p{};
-  const int G = block / group;
+  const int G = block / group, m = h_q / h_kv;
+  int64_t capacity_tiles = 0;   // 256 x 128 tiles of one query head each
+  double loaded = 0, pairs = 0; // LDS rows loaded per stage, and group pairs stored, by all tiles
   for (int r = 0; r < batch; ++r) {
-    const int64_t nqg = (n_q[r] + group - 1) / group, nkg = (n_kv[r] + group - 1) / group;
-    const int64_t rt = (nqg + kScoreTileM - 1) / kScoreTileM;
-    const int64_t ct = (nkg + kScoreTileN - 1) / kScoreTileN;
-    p.total_tiles += (int64_t)h_q * rt * ct;
-    // tile (ti, tj) holds a causal block pair iff its first KV block starts
-    // at or before the end of its last query block: tj * kScoreTileN / G <= E
-    // with E = e_i / b, i.e. tj <= E * G / kScoreTileN
+    const ScoreGrid tg(n_q[r], n_kv[r], group, m);
     const int64_t n_c = n_kv[r] - n_q[r];
-    for (int64_t ti = 0; ti < rt; ++ti) {
-      const int64_t i_max = (std::min(nqg, (ti + 1) * kScoreTileM) - 1) / G;
+    p.total_tiles += (int64_t)h_kv * tg.tiles();
+    capacity_tiles += (int64_t)h_q * ((tg.nqg + kScoreTileM - 1) / kScoreTileM) * tg.nct;
+    for (int64_t rt = 0; rt < tg.nrt; ++rt) {
+      // a row tile's causal column tiles: those whose first KV block starts at
+      // or before the end of its last query block
+      const int64_t u1 = std::min<int64_t>(tg.nu, (rt + 1) * kScoreUnits);
+      const int64_t blk = (u1 - 1) / m;
+      const int64_t i_max = (std::min<int64_t>(tg.nqg, (blk + 1) * kScoreUnit) - 1) / G;
       const int64_t e_i = std::min(n_c + (i_max + 1) * block - 1, (int64_t)n_kv[r] - 1);
-      p.causal_tiles += (int64_t)h_q * std::min(ct, (e_i / block) * G / kScoreTileN + 1);
+      const int64_t cols = std::min<int64_t>(tg.nkg, (e_i / block + 1) * G);
+      const int64_t ct = (cols + kScoreTileN - 1) / kScoreTileN;
+      const double rows =
+          std::min<double>((double)(u1 - rt * kScoreUnits) * kScoreUnit, (double)m * tg.nqg);
+      p.causal_tiles += h_kv * ct;
+      loaded += (double)h_kv * (rows * (double)ct + (double)cols);
+      pairs += (double)h_kv * rows * (double)cols;
     }
   }
   // Estimated time of split S (whole chains per part only): a launch of T
   // causal tiles runs ceil(S T / 256) rounds of workgroups (one per compute
-  // unit of an MI355X) of n_stage / S stages each, a stage of a 256 x 128
-  // tile taking about 1.3 us (its 48 KiB of loads are bound by misses in
-  // flight); a split also writes and re-reads 128 KiB of partial sums per
-  // tile and part, at about 5 TB/s.
+  // unit of an MI355X), each about 3 us to fill and drain and n_stage / S
+  // stages.  A stage takes about 0.45 us plus 0.7 us for the loads of a full
+  // tile (384 rows; 128K: 1.15 us a stage, chunks of 64 rows and fewer over
+  // long prefixes: 0.75 us).  A split also writes and re-reads 4 bytes per
+  // group pair and part, at about 5 TB/s.
   constexpr int kCUs = 256;
-  constexpr double kStageUs = 1.3, kPartialUs = 2.0 * 128 * 1024 / 5e6;
   const int n_stage = group * head_dim / kScoreChunk;
+  const double stage_us =
+      0.45 + 0.7 * loaded / ((double)p.causal_tiles * (kScoreTileM + kScoreTileN));
   auto cost = [&](int s) {
     const double rounds = (double)((p.causal_tiles * s + kCUs - 1) / kCUs);
-    return rounds * (n_stage / s) * kStageUs +
-           (s > 1 ? (double)s * (double)p.causal_tiles * kPartialUs : 0.0);
+    return rounds * (n_stage / s * stage_us + 3.0) + (s > 1 ? s * pairs * 8.0 / 5e6 : 0.0);
   };
-  // a split must save at least 10 % of the estimate to be taken
+  // a split must save at least 10 % of the estimate to be taken, and its
+  // partial sums (room for the tiles of every query head on its own) must
+  // stay within 300 MB
+  const size_t part_bytes = (size_t)capacity_tiles * kScoreTileM * kScoreTileN * sizeof(float);
   double best = 0.9 * cost(1);
   p.split = 1;
-  for (int s = 2; s <= 8; s *= 2) {
-    if (n_stage % (s * kScoreChain) != 0) break;
+  for (int s = 2; s <= 16; s *= 2) {
+    if (n_stage % (s * kScoreChain) != 0 || s * part_bytes > 300000000u) break;
     const double c = cost(s);
     if (c < best) {
       best = c;
       p.split = s;
     }
   }
-  p.partial_bytes = p.split > 1 ? (size_t)p.split * (size_t)p.total_tiles * kScoreTileM *
-                                      kScoreTileN * sizeof(float)
-                                : 0;
+  p.partial_bytes = p.split > 1 ? p.split * part_bytes : 0;
   return p;
 }
 

@@ -1,0 +1,96 @@
+"""Block scores of Stage 1 against float64 matrix products, at the edges of the
+score tiles: row units of 32 query groups that end inside a tile, GQA sizes
+that do not divide the 8 units of a row tile, column tiles of 128 key groups
+with a remainder, every pooling factor, split and unsplit, chunked, paged, and
+token rows that overlap (stride below head_dim)."""
+import pytest
+import torch
+
+from paper_2605_12193_amd import bfla
+
+pytestmark = pytest.mark.gpu
+
+# worst alpha-scaled error of the two-level float sums over 16K products: 8e-6
+# in an emulation of the MFMA order on unit-normal data
+BAR = 2e-5
+
+
+def _ref(q, k, block, group, n_c):
+    """[H_q, L_q, L_kv] block scores of one request, -inf where not causal."""
+    (h_q, n_q, c), (h_kv, n_kv, _) = q.shape, k.shape
+    G, lq, lkv = block // group, -(-n_q // block), -(-n_kv // block)
+
+    def groups(x, blocks):
+        pad = torch.zeros(x.shape[0], blocks * block, c, dtype=torch.float64, device=x.device)
+        pad[:, :x.shape[1]] = x.double()
+        return pad.view(x.shape[0], blocks * G, group * c)
+
+    gq, gk = groups(q, lq), groups(k, lkv)
+    real = (torch.arange(lq * G, device=q.device)[:, None] * group < n_q) & \
+           (torch.arange(lkv * G, device=q.device)[None] * group < n_kv)
+    end = torch.clamp(n_c + (torch.arange(lq, device=q.device) + 1) * block - 1, max=n_kv - 1)
+    causal = torch.arange(lkv, device=q.device)[None] * block <= end[:, None]
+    out = []
+    for p in range(h_q):
+        s = (gq[p] @ gk[p // (h_q // h_kv)].t()).masked_fill(~real, float("-inf"))
+        s = s.view(lq, G, lkv, G).amax(dim=(1, 3))
+        out.append(s.masked_fill(~causal, float("-inf")))
+    return torch.stack(out)
+
+
+@pytest.mark.parametrize("n_q,n_kv,h_q,h_kv,c,block,group,paged,overlap", [
+    ([2048], [2048], 1, 1, 64, 128, 64, 0, False),         # one unit, split 8
+    ([2081], [2081], 6, 2, 64, 128, 64, 0, False),         # 33 groups: a unit of one group
+    ([8256, 65], [8256, 8300], 5, 1, 128, 128, 64, 16, False),   # 129 groups: columns 128 + 1
+    ([130], [20011], 8, 1, 128, 256, 64, 32, False),       # a chunk of 3 groups, long prefix
+    ([4500], [4500], 7, 1, 64, 1024, 64, 0, False),        # G = 16
+    ([3000], [3777], 6, 2, 64, 512, 64, 0, False),         # G = 8, chunked
+    ([16400], [16400], 3, 1, 128, 64, 64, 0, False),       # G = 1, 257 blocks
+    ([2500], [2500], 4, 2, 64, 128, 16, 16, False),        # pages as long as a group
+    ([1000], [1000], 4, 2, 64, 128, 128, 16, False),       # eight pages in a group
+    ([777], [1990], 4, 2, 128, 128, 64, 0, True)])         # overlapping token rows
+@pytest.mark.parametrize("copies", [1, 16])   # a larger batch: other splits, none at all
+def test_block_scores(n_q, n_kv, h_q, h_kv, c, block, group, paged, overlap, copies):
+    n_q, n_kv = n_q * copies, n_kv * copies
+    gen = torch.Generator(device="cuda").manual_seed(sum(n_kv) + c)
+    st = c // 2 if overlap else c
+    mk = lambda h, n: torch.as_strided(
+        torch.randn(h * n * c, device="cuda", generator=gen).to(torch.bfloat16), (h, n, c),
+        (n * c, st, 1))
+    prm = bfla.params(block=block, group=group)
+    prob = bfla.Problem(n_q, n_kv, h_q, h_kv, c)
+    q, k = mk(h_q, sum(n_q)), mk(h_kv, sum(n_kv))
+    qs = [sum(n_q[:r]) for r in range(len(n_q))]
+    ks = [sum(n_kv[:r]) for r in range(len(n_kv))]
+    qv = bfla.View(q, q.stride(0), q.stride(1), batch_offsets=[s * st for s in qs])
+    if paged:
+        pages = [-(-n // paged) for n in n_kv]
+        perm = torch.randperm(sum(pages), device="cuda", generator=gen)
+        table = torch.full((len(n_kv), max(pages)), -1, dtype=torch.int32, device="cuda")
+        pool = torch.zeros(sum(pages), paged, h_kv, c, dtype=torch.bfloat16, device="cuda")
+        at = 0
+        for r, n in enumerate(n_kv):
+            ids = perm[at:at + pages[r]]
+            table[r, :pages[r]] = ids.int()
+            at += pages[r]
+            x = torch.zeros(pages[r] * paged, h_kv, c, dtype=torch.bfloat16, device="cuda")
+            x[:n] = k[:, ks[r]:ks[r] + n].transpose(0, 1)
+            pool[ids] = x.view(pages[r], paged, h_kv, c)
+        kv = bfla.KV(pool, pool, paged=True, block_table=table)
+    else:
+        kv = bfla.KV(k, k, batch_offsets=[s * st for s in ks])
+    buf = bfla.Buffers(prob, prm)
+    buf.scores.fill_(float("nan"))
+    buf.ws_estimate.fill_(0xFF)   # NaN partial sums: any that are read must have been written
+    bfla.bfla_estimate_mask(prob, prm, qv, kv, buf.block_mask, dbg_scores=buf.scores,
+                            workspace=buf.ws_estimate)
+    torch.cuda.synchronize()
+    off = 0
+    for r, (a, n) in enumerate(zip(n_q, n_kv)):
+        want = _ref(q[:, qs[r]:qs[r] + a], k[:, ks[r]:ks[r] + n], block, group, n - a)
+        got = buf.scores[off:off + want.numel()].view(want.shape).double()
+        off += want.numel()
+        assert torch.equal(torch.isinf(got), torch.isinf(want))
+        fin = ~torch.isinf(want)
+        err = ((got - want)[fin].abs().max() * c ** -0.5).item()
+        assert err <= BAR, (r, err)
