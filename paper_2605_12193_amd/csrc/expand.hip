@@ -7,10 +7,15 @@
 //           | sink kt < n_sink                            (eq22)
 //   rescued = !kept & (chi(qt, kt; s) mod eta == 0        (eq24)
 //                      | psi(h, qt, kt; s) < rho)         (eq25)
-// Pass 1 stores the wave ballots (one 64-bit word per 64 tiles of a row) and
-// the row counts; pass 2 is an exclusive scan of the counts in one
-// workgroup; pass 3 reads the ballots back and writes each kept tile at its
-// list position, so every keep / drop decision is taken once.
+// count_kernel stores the wave ballots (one 64-bit word per 64 tiles of a row)
+// and the total of each workgroup's rows; scatter_kernel adds the totals of the
+// workgroups before its own, reads the ballots back and writes row_ptr and
+// each kept tile at its list position, so every keep / drop decision is
+// taken once.  Up to some 10K rows the two launches are what this costs (4-5
+// us each); a scan kernel between them runs only where the totals are too
+// many to add up in every workgroup (it took 2-5 us there, 23 us for the
+// 16,384 rows of a 128K layer, one total per row).  Both passes in a single
+// workgroup for few rows were slower (2K tokens, 64 rows: 10.6 us against 7.5).
 #include <algorithm>
 #include <atomic>
 
@@ -27,15 +32,20 @@ namespace bfla {
 namespace {
 
 constexpr int TILE = 64;
-constexpr int ROWS_PER_WG = 4;
+constexpr int ROWS_PER_WG = 8;
 constexpr int SCAN_THREADS = 1024;
+// Totals that every workgroup of scatter_kernel adds up by itself (16 KB, four
+// loads of a thread's 16 bytes); beyond, a scan kernel turns them into offsets.
+constexpr int DIRECT_TOTALS = 4096;
 
 struct ExpandArgs {
   const uint8_t* block_mask;
   int32_t* row_ptr;
   int32_t* cols;
-  int32_t* counts;
+  int32_t* totals;   // kept tiles of each workgroup's rows (after a scan: of those before)
   uint64_t* bits;
+  int32_t wg_lo;     // this launch's first workgroup among all of the call
+  int32_t scanned;   // totals are offsets already
   int32_t words_per_row;
   int32_t n_rows;
   int32_t h_kv, rb;
@@ -57,7 +67,7 @@ __host__ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 
 struct RowCtx {
   const uint8_t* blk_row;  // block mask row of this q-tile's query block
-  int h, qt, kt_diag, n_tiles;
+  int h, qt, kt_diag, n_tiles;   // n_tiles: causal tiles
 };
 
 __device__ __forceinline__ bool row_ctx(const ExpandArgs& a, int row, RowCtx* c) {
@@ -100,29 +110,62 @@ __device__ __forceinline__ bool keep_tile(const ExpandArgs& a, const RowCtx& c, 
   return false;
 }
 
-__global__ void __launch_bounds__(64 * ROWS_PER_WG) count_kernel(ExpandArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int row = a.row_lo + blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 6);
-  RowCtx c;
-  if (!row_ctx(a, row, &c)) return;
-  uint64_t* bits = a.bits + (int64_t)row * a.words_per_row;
+// Decides the causal tiles of one row (one wave): ballots to `bits`, and the
+// number kept.
+__device__ __forceinline__ int decide_row(const ExpandArgs& a, const RowCtx& c, uint64_t* bits,
+                                          int lane) {
   int total = 0;
   for (int k0 = 0; k0 < c.n_tiles; k0 += 64) {
     const uint64_t b = __ballot(keep_tile(a, c, k0 + lane));
     if (lane == 0) bits[k0 >> 6] = b;
     total += __popcll(b);
   }
-  if (lane == 0) a.counts[row] = total;
+  return total;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(const int32_t* counts,
-                                                            int32_t* row_ptr, int n) {
+// Writes the kept tiles of one row (one wave) from position pos on.
+__device__ __forceinline__ void write_row(const ExpandArgs& a, const RowCtx& c,
+                                          const uint64_t* bits, int pos, int lane) {
+  for (int k0 = 0; k0 < c.n_tiles; k0 += 64) {
+    const uint64_t b = bits[k0 >> 6];
+    const bool keep = (b >> lane) & 1;
+    const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+    if (keep) a.cols[pos + before] = k0 + lane;
+    pos += __popcll(b);
+  }
+}
+
+__device__ __forceinline__ int wave_sum(int x) {
+  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
+  return x;
+}
+
+__global__ void __launch_bounds__(64 * ROWS_PER_WG) count_kernel(ExpandArgs a) {
+  __shared__ int cnt[ROWS_PER_WG];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = a.row_lo + blockIdx.x * ROWS_PER_WG + wave;
+  RowCtx c;
+  int n = 0;
+  if (row_ctx(a, row, &c)) n = decide_row(a, c, a.bits + (int64_t)row * a.words_per_row, lane);
+  if (lane == 0) cnt[wave] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int t = 0;
+    for (int w = 0; w < ROWS_PER_WG; ++w) t += cnt[w];
+    a.totals[a.wg_lo + blockIdx.x] = t;
+  }
+}
+
+// Exclusive scan of the workgroup totals in place, for calls with more than
+// DIRECT_TOTALS of them.
+__global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(int32_t* totals, int n) {
   __shared__ int32_t wsum[SCAN_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (n + SCAN_THREADS - 1) / SCAN_THREADS;
   const int beg = min(n, tid * per), end = min(n, beg + per);
   int s = 0;
-  for (int i = beg; i < end; ++i) s += counts[i];
+  for (int i = beg; i < end; ++i) s += totals[i];
   // inclusive scan of s across the workgroup
   int x = s;
   for (int d = 1; d < 64; d <<= 1) {
@@ -142,28 +185,44 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(const int32_t* count
   __syncthreads();
   int excl = x - s + (wave > 0 ? wsum[wave - 1] : 0);
   for (int i = beg; i < end; ++i) {
-    row_ptr[i] = excl;
-    excl += counts[i];
+    const int t = totals[i];
+    totals[i] = excl;
+    excl += t;
   }
-  if (tid == SCAN_THREADS - 1) row_ptr[n] = wsum[SCAN_THREADS / 64 - 1];
 }
 
 __global__ void __launch_bounds__(64 * ROWS_PER_WG) scatter_kernel(ExpandArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int row = a.row_lo + blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 6);
+  __shared__ int cnt[ROWS_PER_WG], part[ROWS_PER_WG];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wg = a.wg_lo + blockIdx.x;
+  const int row = a.row_lo + blockIdx.x * ROWS_PER_WG + wave;
   RowCtx c;
-  if (!row_ctx(a, row, &c)) return;
+  const bool live = row_ctx(a, row, &c);
   const uint64_t* bits = a.bits + (int64_t)row * a.words_per_row;
-  int pos = a.row_ptr[row];
-  for (int k0 = 0; k0 < c.n_tiles; k0 += 64) {
-    const int kt = k0 + lane;
-    const uint64_t b = bits[k0 >> 6];   // pass 1's ballot of these 64 tiles
-    const bool keep = (b >> lane) & 1;
-    int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
-                                           __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
-    if (keep) a.cols[pos + before] = kt;
-    pos += __popcll(b);
+  // kept tiles of this row, and of the workgroups before this one
+  int n = 0, before = 0;
+  if (live)
+    for (int w = lane; w < (c.n_tiles + 63) >> 6; w += 64) n += __popcll(bits[w]);
+  if (!a.scanned)
+    for (int i = threadIdx.x; i < wg; i += 64 * ROWS_PER_WG) before += a.totals[i];
+  n = wave_sum(n);
+  before = wave_sum(before);
+  if (lane == 0) {
+    cnt[wave] = n;
+    part[wave] = before;
   }
+  __syncthreads();
+  int pos = a.scanned ? a.totals[wg] : 0;
+  for (int w = 0; w < ROWS_PER_WG; ++w) {
+    if (!a.scanned) pos += part[w];
+    if (w < wave) pos += cnt[w];
+  }
+  if (!live) return;
+  if (lane == 0) {
+    a.row_ptr[row] = pos;
+    if (row == a.n_rows - 1) a.row_ptr[a.n_rows] = pos + n;
+  }
+  write_row(a, c, bits, pos, lane);
 }
 
 }  // namespace
@@ -198,7 +257,7 @@ hipError_t launch_expand(const ExpandLaunch& L, hipStream_t stream) {
   a.block_mask = L.block_mask;
   a.row_ptr = L.row_ptr;
   a.cols = L.cols;
-  a.counts = L.counts;
+  a.totals = L.counts;   // at most one per row
   a.bits = L.bits;
   a.words_per_row = L.words_per_row;
   a.n_rows = L.n_rows;
@@ -212,8 +271,10 @@ hipError_t launch_expand(const ExpandLaunch& L, hipStream_t stream) {
   a.chi_key = mix64(L.seed);
   a.psi_key = mix64(L.seed + 1);
   // count and scatter once per group of kLaunchRequests requests (each over
-  // its own rows), one scan over every row in between
+  // its own rows and workgroups)
+  int n_wg = 0;
   auto for_each_group = [&](auto&& launch) -> hipError_t {
+    n_wg = 0;
     for (size_t g0 = 0; g0 < L.reqs.size(); g0 += kLaunchRequests) {
       const int n = (int)std::min<size_t>(kLaunchRequests, L.reqs.size() - g0);
       a.batch.n_req = n;
@@ -223,20 +284,25 @@ hipError_t launch_expand(const ExpandLaunch& L, hipStream_t stream) {
       a.row_hi = last.row_base + L.h_kv * last.t_q;
       if (a.row_hi == a.row_lo) continue;
       const int grid = (a.row_hi - a.row_lo + ROWS_PER_WG - 1) / ROWS_PER_WG;
+      a.wg_lo = n_wg;
       launch(grid);
+      n_wg += grid;
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   };
+  a.scanned = 0;
   hipError_t e = for_each_group([&](int grid) {
     hipLaunchKernelGGL(count_kernel, dim3(grid), dim3(64 * ROWS_PER_WG), 0, stream, a);
   });
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, stream, a.counts, a.row_ptr,
-                     a.n_rows);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (n_wg > DIRECT_TOTALS) {
+    a.scanned = 1;
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, stream, a.totals, n_wg);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   return for_each_group([&](int grid) {
     hipLaunchKernelGGL(scatter_kernel, dim3(grid), dim3(64 * ROWS_PER_WG), 0, stream, a);
   });
