@@ -1,0 +1,370 @@
+// Device code shared by the prefill kernels: arguments, LDS and MFMA
+// primitives, paged addressing, the order of a launch's rows.
+#pragma once
+
+#include <atomic>
+#include <utility>
+
+#include "bfla_device.h"
+#include "bfla_internal.h"
+
+namespace bfla {
+
+struct PrefillArgs {
+  const bf16_t* q;
+  bf16_t* o;
+  float* lse;
+  const int32_t* row_ptr;  // sparse lists (unused when dense)
+  const int32_t* cols;
+  int64_t q_sh, q_st, o_sh, o_st;
+  KvAddr kv;
+  int32_t h_q, h_kv, m;
+  float scale;
+  float c2;                // scale * log2(e), as a kernel argument (a scalar register)
+  int32_t by_length;       // sparse: rows of a band run longest list first
+  Batch batch;
+};
+
+// Work items per list row of the shapes that prefill_units_kernel takes (0:
+// prefill_kernel or prefill_q16_kernel).
+constexpr int units_parts(int c, int m) {
+  return (c == 128 && m == 5) || (c == 64 && (m == 3 || m == 5)) ? 1 : c == 64 && m == 6 ? 2 : 0;
+}
+hipError_t launch_prefill_units(const PrefillArgs& a, int head_dim, bool dense, int n_work,
+                                hipStream_t s);
+
+namespace {
+
+constexpr int TILE = 64;
+constexpr float LOG2E = 1.4426950408889634f;
+constexpr int RESCALE_LOG2 = 8;
+constexpr float RESCALE_SUM = float(1 << RESCALE_LOG2);
+constexpr uint32_t RSRC_WORD3 = 0x00020000u;  // raw buffer, 32-bit data format
+constexpr int VMCNT0 = 0x0F70;                // s_waitcnt vmcnt(0), other counters free
+
+template <int C>
+struct Cfg {
+  static constexpr int KROW = C + 8;          // K tile row pitch (bf16), padded
+  static constexpr int VROW = TILE + 8;       // V^T row pitch (bf16), padded
+  static constexpr int K_ELEMS = TILE * KROW;
+  static constexpr int V_ELEMS = C * VROW;
+  static constexpr int STAGE = K_ELEMS + V_ELEMS;
+  // three stages (ping-pong schedule) when they fit the 160 KB of LDS
+  static constexpr bool PING_PONG = 3 * STAGE * 2 <= 160 * 1024;
+  static constexpr int K_CHUNKS = TILE * C / 8;   // 16-byte chunks per K tile
+  static constexpr int V_UNITS = (TILE / 2) * (C / 8);  // key pairs x 8 channels
+};
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ uint4 ld16(const bf16_t* p) {
+  return *reinterpret_cast<const uint4*>(p);
+}
+
+__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// Two floats -> two bf16 (round to nearest even) in one word.
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+  f32x2 x = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+}
+
+// max / sum of x over lanes l and l ^ 32, in every lane, without going
+// through LDS: v_permlane32_swap leaves x of lane l % 32 in one result and
+// x of lane 32 + l % 32 in the other.
+__device__ __forceinline__ f32x2 lane32_pair(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x),
+                                                  __builtin_bit_cast(uint32_t, x), false, false);
+  return f32x2{__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])};
+}
+__device__ __forceinline__ float max_lane32(float x) {
+  const f32x2 p = lane32_pair(x);
+  return fmaxf(p[0], p[1]);
+}
+__device__ __forceinline__ float add_lane32(float x) {
+  const f32x2 p = lane32_pair(x);
+  return p[0] + p[1];
+}
+
+// Position of key offset k (0..63) inside the permuted V^T row.
+__device__ __forceinline__ int vperm(int k) {
+  return (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1);
+}
+
+// Uniform reads of the tile lists through the constant address space, so
+// they become scalar loads (a vector load would be waited on together with the
+// in-flight K/V prefetch).
+typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+__device__ __forceinline__ int uniform_load(const int32_t* p, int i) {
+  return ((const_i32_ptr)p)[i];
+}
+
+// A block-table entry at byte offset e of a row, read as a scalar.  Through
+// readfirstlane: a plain load that feeds a select is sunk into a branch of
+// its own, and loads between branches are not issued together, which costs
+// one round trip per entry.
+__device__ __forceinline__ uint32_t table_entry(const int32_t* row, uint32_t e) {
+  typedef const __attribute__((address_space(4))) char* const_byte_ptr;
+  return (uint32_t)__builtin_amdgcn_readfirstlane(*(const_i32_ptr)((const_byte_ptr)row + e));
+}
+
+// Paged K/V: a 64-key tile spans up to four pages (pages hold >= 16 tokens).
+// Its keys are addressed as if the tile were contiguous, boff = (kr * st +
+// 8 ce) * 2 for key kr, plus the base of the key's page slot j = kr / ps
+// (0 when ps >= 64): base_j = pg_j * page_bytes + (tok0 % ps) * st * 2 -
+// j * ps * st * 2.  An entry outside [0, n_pages) gives 2^31, past every
+// descriptor's range, so its keys read zeros; rows counts the keys of the
+// tile below N_kv, and V units past it are zeroed the same way.  (Named
+// fields, not an array: per-lane picks among them must stay selects between
+// registers, not indexed scratch loads.)
+struct PageBases {
+  uint32_t b0, b1, b2, b3;
+  int rows;
+};
+// Tile kt of a request whose block-table row is bt (N_kv >= 1).  Tiles
+// outside [0, T_kv) (past the end of a list, or malformed lists) get rows = 0
+// and bases of 2^31: their loads read zeros without memory traffic.  The
+// four entries from the tile's first page on are read unconditionally,
+// clamped to the request's last page, and issued together; slots past the
+// tile or past N_kv are never used for keys below N_kv.
+__device__ __forceinline__ PageBases page_bases(const int32_t* bt, int kt, int t_kv, int n_kv,
+                                                int ps_shift, uint32_t n_pages,
+                                                uint32_t page_bytes, uint32_t tok_bytes) {
+  const bool ok = (unsigned)kt < (unsigned)t_kv;
+  const int tok0 = ok ? kt * TILE : 0;
+  PageBases pb;
+  pb.rows = ok ? min(n_kv - tok0, TILE) : 0;
+  const uint32_t in_page = (uint32_t)(tok0 & ((1 << ps_shift) - 1)) * tok_bytes;
+  const uint32_t slot_step = tok_bytes << ps_shift;
+  const uint32_t e0 = (uint32_t)(tok0 >> ps_shift) * 4u;
+  const uint32_t last_e = (uint32_t)((n_kv - 1) >> ps_shift) * 4u;
+  uint32_t pg[4], b[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) pg[j] = table_entry(bt, min(e0 + 4u * j, last_e));
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    b[j] = ok && pg[j] < n_pages ? pg[j] * page_bytes + in_page - (uint32_t)j * slot_step
+                                 : 0x80000000u;
+  pb.b0 = b[0];
+  pb.b1 = b[1];
+  pb.b2 = b[2];
+  pb.b3 = b[3];
+  return pb;
+}
+// The four bases in lanes 0-3 of one register, written whatever the exec
+// mask (the other lanes are unused): a wave whose K rows of a round lie in
+// one page reads its base with one readlane.
+__device__ __forceinline__ int page_lanes(const PageBases pb) {
+  int vb;
+  asm("v_writelane_b32 %0, %1, 0" : "=v"(vb) : "s"(pb.b0));
+  asm("v_writelane_b32 %0, %1, 1" : "+v"(vb) : "s"(pb.b1));
+  asm("v_writelane_b32 %0, %1, 2" : "+v"(vb) : "s"(pb.b2));
+  asm("v_writelane_b32 %0, %1, 3" : "+v"(vb) : "s"(pb.b3));
+  return vb;
+}
+// V: a thread's key pair (2 j, 2 j + 1) lies in one page slot (hi, lo bits
+// of the slot index, fixed per thread); the base of each key, or 2^31 for a
+// key past N_kv.
+__device__ __forceinline__ void v_pair_bases(const PageBases pb, bool hi, bool lo, int key0,
+                                             uint32_t& b_first, uint32_t& b_second) {
+  const uint32_t bv = hi ? (lo ? pb.b3 : pb.b2) : (lo ? pb.b1 : pb.b0);
+  b_first = key0 < pb.rows ? bv : 0x80000000u;
+  b_second = key0 + 1 < pb.rows ? bv : 0x80000000u;
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes,
+                                           (int)RSRC_WORD3);
+}
+
+__device__ __forceinline__ uint4 bload16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
+// every lambda of the kernel body is inlined (the loop calls some of them
+// from several places, which the inliner would otherwise turn into calls)
+#define INLINE __attribute__((always_inline))
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+#define LDS_ADDR(arr) ((uint32_t)(uintptr_t)(lds_ptr_t)(arr))
+
+// f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>),
+// so that the body can use its index as a constant (immediate operands).
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// 16-byte LDS read issued exactly where it stands.  The result is in flight
+// until a later lgkm_wait on the same value; the compiler does not track it.
+template <int OFF>
+__device__ __forceinline__ void lds_read(u32x4& r, uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "ds_read offset field is 16 bits");
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF) : "memory");
+}
+// Wait until at most N LDS/scalar-memory operations are outstanding.  r is an
+// in/out operand so that no use of r can move above the wait.  LDS operations
+// complete in issue order, so waiting for N leaves only the last N reads
+// pending; other LDS or scalar loads in flight can only make it stricter.
+template <int N>
+__device__ __forceinline__ void lgkm_wait(u32x4& r) {
+  static_assert(N >= 0 && N < 16, "lgkmcnt field is 4 bits");
+  asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(r) : "i"(N));
+}
+
+// Order of a sparse launch's rows (PrefillArgs::by_length).  With KV head and
+// blockIdx both taken modulo 8, an XCD works on one KV head: about 32 rows at a
+// time, all walking their lists up from tile 0.  Their common tiles are read
+// from L2 only while the rows stay within its 4 MB of each other (128 tiles
+// at C = 128).  In q-tile order they do not: list lengths vary by some 7 %
+// between neighbouring rows, so after a few rows the workgroups of an XCD
+// stand at unrelated places.  Taking the rows of every band of 64 q-tiles
+// longest list first keeps them in step (the next 32 rows are of nearly one
+// length, so they start and end together): the 128K 32/8-head layer (rho 0.1)
+// hits L2 on 66 % of its requests instead of 22 % and runs in 22.9 ms a pass
+// instead of 23.8, 32K 1.286 instead of 1.315 ms, 64K with C = 256 4.53
+// instead of 4.70 ms (one box, both sides alternating).
+//
+// Each wave finds its row by itself, without a workspace: lane l of the band
+// reads the list bounds of its l-th row, and the idx-th longest (equal
+// lengths in q-tile order) is selected by the bits of the lengths, from the
+// top.  The 12 highest bits a length of this request can have take part;
+// they order rows of up to 4095 tiles exactly and longer ones to within the
+// dropped bits, and any lengths (malformed lists too) give a permutation.
+struct RowPick {
+  int qt, list_begin, n_tiles;
+};
+__device__ __forceinline__ RowPick pick_row(const int32_t* row_ptr, int row0, int t_q, int t_kv,
+                                            int idx, int lane) {
+  const int top = t_q - (idx & ~63);        // one past the band's last q-tile
+  const int nb = min(top, 64);              // rows of the band: lane l has q-tile top - 1 - l
+  const int r = row0 + top - 1 - min(lane, nb - 1);
+  const int beg = row_ptr[r];
+  const uint32_t len = (uint32_t)(row_ptr[r + 1] - beg);
+  constexpr int BITS = 12;
+  const int shift = max(0, 32 - __builtin_clz((uint32_t)t_kv) - BITS);
+  uint64_t set[BITS];
+#pragma unroll
+  for (int j = 0; j < BITS; ++j) set[j] = __builtin_amdgcn_ballot_w64((len >> (shift + j)) & 1u);
+  uint64_t in = __builtin_amdgcn_ballot_w64(lane < nb);
+  int k = idx & 63;
+#pragma unroll
+  for (int j = BITS - 1; j >= 0; --j) {
+    const uint64_t one = set[j] & in;
+    const int n = __builtin_popcountll(one);
+    in = k < n ? one : in & ~set[j];
+    k = k < n ? k : k - n;
+  }
+  // the k-th lane left
+  const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0));
+  const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(before == k) & in);
+  return {top - 1 - l, __builtin_amdgcn_readlane(beg, l),
+          __builtin_amdgcn_readlane((int)len, l)};
+}
+
+template <bool PAGED>
+struct KvTiles {
+  int t_kv, n_kv;
+  uint32_t tile_bytes;     // contiguous: bytes per 64-key tile
+  const int32_t* bt;       // paged: this request's block-table row
+  int ps_shift;
+  uint32_t n_pages, page_bytes, tok_bytes;
+  int64_t st;              // elements per token
+
+  // Contiguous: b0 is the tile's first byte (2^31 for a tile outside
+  // [0, T_kv), so its loads read zeros).  Paged: page_bases().
+  __device__ __forceinline__ PageBases locate(int kt) const {
+    if (PAGED) return page_bases(bt, kt, t_kv, n_kv, ps_shift, n_pages, page_bytes, tok_bytes);
+    PageBases pb{};
+    pb.b0 = (unsigned)kt < (unsigned)t_kv ? (uint32_t)kt * tile_bytes : 0x80000000u;
+    return pb;
+  }
+};
+template <int C, bool PAGED>
+__device__ __forceinline__ KvTiles<PAGED> kv_tiles(const PrefillArgs& a, const ReqDesc& Rd, int h,
+                                                   __amdgpu_buffer_rsrc_t& krs,
+                                                   __amdgpu_buffer_rsrc_t& vrs) {
+  KvTiles<PAGED> kt;
+  kt.t_kv = Rd.t_kv;
+  kt.n_kv = Rd.n_kv;
+  kt.st = a.kv.stride_tok;
+  kt.tile_bytes = (uint32_t)(TILE * kt.st * 2);
+  if (!PAGED) {
+    const int64_t head_off = Rd.kv_off + (int64_t)h * a.kv.stride_head;
+    const uint32_t bytes = (uint32_t)(((int64_t)(Rd.n_kv - 1) * kt.st + C) * 2);
+    krs = make_rsrc(a.kv.k + head_off, bytes);
+    vrs = make_rsrc(a.kv.v + head_off, bytes);
+    kt.bt = nullptr;
+    kt.ps_shift = 0;
+    kt.n_pages = kt.page_bytes = kt.tok_bytes = 0;
+  } else {
+    const int64_t head_off = (int64_t)h * a.kv.stride_head;
+    krs = make_rsrc(a.kv.k + head_off, a.kv.pool_bytes);
+    vrs = make_rsrc(a.kv.v + head_off, a.kv.pool_bytes);
+    kt.bt = a.kv.block_table + (int64_t)Rd.bt_row * a.kv.max_pages;
+    kt.ps_shift = __builtin_ctz(a.kv.page_size);   // power of two >= 16
+    kt.n_pages = (uint32_t)a.kv.n_pages;
+    kt.page_bytes = (uint32_t)(a.kv.page_stride * 2);
+    kt.tok_bytes = (uint32_t)(kt.st * 2);
+  }
+  return kt;
+}
+
+// ---- head dim 256: 16-query waves on v_mfma_f32_16x16x32_bf16 ----
+__device__ __forceinline__ f32x4 mfma16x16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x2 lane16_pair(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x),
+                                                  __builtin_bit_cast(uint32_t, x), false, false);
+  return f32x2{__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])};
+}
+__device__ __forceinline__ float max_lane4(float x) {
+  const f32x2 p = lane32_pair(x);
+  const f32x2 q = lane16_pair(fmaxf(p[0], p[1]));
+  return fmaxf(q[0], q[1]);
+}
+__device__ __forceinline__ float add_lane4(float x) {
+  const f32x2 p = lane32_pair(x);
+  const f32x2 q = lane16_pair(p[0] + p[1]);
+  return q[0] + q[1];
+}
+// key 32 c + 16 h + 4 g + r of a tile sits at 32 c + 8 g + 4 h + r of a V^T
+// row: the k order of the 16x16x32 B operand built from the S layout
+__device__ __forceinline__ int vperm16(int k) {
+  return (k & 32) | (((k >> 2) & 3) << 3) | (((k >> 4) & 1) << 2) | (k & 3);
+}
+
+// Launch one instantiation with `lds` bytes of dynamic LDS.  The kernel's
+// dynamic-LDS limit is raised once per device (bit d of its mask); setting
+// it is idempotent, so two threads racing on a device both set it.
+template <auto KERN>
+hipError_t launch_kernel(const PrefillArgs& a, int n_work, int threads, int lds, hipStream_t s) {
+  static std::atomic<uint64_t> attr_set{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
+  if (!bit || !(attr_set.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_set.fetch_or(bit, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(KERN, dim3(n_work), dim3(threads), lds, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace bfla

@@ -1,0 +1,470 @@
+// Prefill for GQA sizes whose heads do not divide into eight equal waves.
+// gfx950 / CDNA4, wave64.
+#include "prefill_device.h"
+
+namespace bfla {
+namespace {
+
+// Work item = one list row (request, KV head, q-tile), or half of its queries
+// (PARTS = 2): its m heads x 4 / PARTS blocks of 16 queries are units, a
+// multiple of the four SIMDs.  Eight waves in two groups, one wave of each per
+// SIMD: a wave of group A (0-3) owns UA units and one of group B (4-7) UB, so
+// every SIMD carries UA + UB units.
+// The groups run the ping-pong of prefill_kernel over three LDS stages; group
+// B, with fewer units, stages every K/V tile.  MFMAs are 16x16x32: a fragment
+// read from LDS feeds all units of the wave, and a lane owns one query of each
+// unit and 16 of the tile's keys.
+//   Why: five waves of 32 queries, one per head over half a q-tile, put two of
+// them on one SIMD (5/8 of the MFMA rate at best) and read each K/V tile once
+// per half.  With 3 + 2 units the paged four-request batch (GQA 5, C = 128,
+// 16K-128K tokens) takes 41.2 ms a pass instead of 59.0, its sparse prefill
+// 1.16 PFLOP/s on the kept tiles instead of 0.81, dense 16K 1.07 instead of
+// 0.89.  At C = 64 the softmax is the larger half, and what counts is waves
+// per SIMD: 2 + 1 units take 128 VGPRs, so two workgroups share a CU.  Dense
+// 16K at C = 64: GQA 3 0.67 -> 0.85 PFLOP/s, GQA 6 (halves) 0.71 -> 0.89, GQA
+// 5 0.61 -> 0.80.  Slower than prefill_kernel, or no faster, in this form: C =
+// 128 GQA 3 (0.89 against 0.95), 4 (0.98, 1.14) and 6 (3 + 3 units spill 92
+// VGPRs); C = 64 GQA 4 (0.78, 0.80), 7 (0.76, 0.78) and 8 (0.74, 0.88).
+//   What bounds it at C = 128: group A's two phases, 96 MFMAs of 16 cycles and
+// the softmax of 48 queries, which a single wave issues at one VALU
+// instruction per 8 cycles.  Its registers are full (254): fragments are read
+// two ahead instead of four (three spilled 6 VGPRs and four 16: 41.5 and 47
+// ms), row sums are kept per lane and added up at the end, and nothing derived
+// from the lane number lives through the loop.  (The row sums in LDS, added
+// with ds_add: 49 ms.)
+template <int C, int M, int PARTS, int UA, int UB, bool DENSE, bool PAGED>
+__global__ void __launch_bounds__(512) prefill_units_kernel(PrefillArgs a) {
+  constexpr int NB = 4 / PARTS;   // 16-query blocks of an item
+  static_assert(4 * (UA + UB) == M * NB, "the units over four SIMDs");
+  using CF = Cfg<C>;
+  constexpr int KROW = CF::KROW, VROW = CF::VROW;
+  constexpr int NKC = C / 32, NCB = C / 16;
+  constexpr int ST = 256;   // staging threads (group B)
+  constexpr int KC = CF::K_CHUNKS / ST, VU = CF::V_UNITS / ST;
+  static_assert(CF::K_CHUNKS % ST == 0 && CF::V_UNITS % ST == 0, "whole staging rounds");
+  constexpr int K_ROW_STEP = ST / (C / 8), V_CE_STEP = ST / (TILE / 2);
+  extern __shared__ __align__(16) bf16_t lds[];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15;
+  const int g = lane >> 4;
+
+  const int w = blockIdx.x;
+  const int ri = find_req(a.batch, w);
+  const ReqDesc& Rd = a.batch.r[ri];
+  const int n_q = Rd.n_q, n_kv = Rd.n_kv, t_q = Rd.t_q, t_kv = Rd.t_kv;
+  const int64_t q_off = Rd.q_off, o_off = Rd.o_off, lse_off = Rd.lse_off;
+  const int local = w - Rd.work_begin;
+  const int h = local % a.h_kv;
+  const int rank = local / a.h_kv;
+  int qt = t_q - 1 - rank / PARTS;
+  const int blk0 = rank % PARTS * NB;   // the item's first block
+  const int n_c = n_kv - n_q;
+  int list_begin = 0, n_tiles;
+  if (DENSE) {
+    n_tiles = min(n_c + (qt + 1) * TILE - 1, n_kv - 1) / TILE + 1;
+  } else if (a.by_length) {
+    const RowPick rp = pick_row(a.row_ptr, Rd.row_base + h * t_q, t_q, t_kv, rank / PARTS, lane);
+    qt = rp.qt;
+    list_begin = rp.list_begin;
+    n_tiles = rp.n_tiles;
+  } else {
+    const int row = Rd.row_base + h * t_q + qt;
+    list_begin = uniform_load(a.row_ptr, row);
+    n_tiles = uniform_load(a.row_ptr, row + 1) - list_begin;
+  }
+  __amdgpu_buffer_rsrc_t krs, vrs;
+  const KvTiles<PAGED> kvt = kv_tiles<C, PAGED>(a, Rd, h, krs, vrs);
+
+  auto tile_or_none = [&](int i) INLINE -> int {
+    if (DENSE) return i < n_tiles ? i : -1;
+    const int tt = __builtin_amdgcn_readfirstlane(
+        uniform_load(a.cols, __builtin_amdgcn_readfirstlane(list_begin + min(i, n_tiles - 1))));
+    return i < n_tiles ? tt : -1;
+  };
+  auto stage = [&](int slot) INLINE -> bf16_t* { return lds + slot * CF::STAGE; };
+
+  const float c2 = a.c2;
+  // The lane number, computed anew where it is used: values derived from it
+  // would be held, and spilled, through the loop.
+  auto lane_now = [&]() INLINE -> int {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+  };
+  const uint32_t lds_base = LDS_ADDR(lds);
+  const uint32_t k_lane = lds_base + (uint32_t)((l16 * KROW + 8 * g) * 2);
+  const uint32_t v_lane = lds_base + (uint32_t)((CF::K_ELEMS + l16 * VROW + 8 * g) * 2);
+  const std::true_type YES;
+  const std::false_type NO;
+
+  // The whole life of a wave of group A or B (U units each); both pass the
+  // same barriers in the same order.
+  auto run = [&](auto is_a) INLINE {
+    constexpr bool A = decltype(is_a)::value;
+    constexpr int U = A ? UA : UB;
+    const int x0 = A ? UA * wave : 4 * UA + UB * (wave - 4);   // first unit of the wave
+
+    // ---- staging (group B) ----
+    const int sid = tid - 256;
+    const int64_t st = kvt.st;
+    const uint32_t st_bytes = (uint32_t)(st * 2);
+    const int k_row = sid / (C / 8), k_ce = sid % (C / 8);
+    const uint32_t k_boff = (uint32_t)(((int64_t)k_row * st + 8 * k_ce) * 2);
+    const uint32_t k_step = (uint32_t)(K_ROW_STEP * st * 2);
+    const int v_j = sid % (TILE / 2), v_ce = sid / (TILE / 2);
+    const uint32_t v_boff = (uint32_t)(((int64_t)(2 * v_j) * st + 8 * v_ce) * 2);
+    constexpr uint32_t V_STEP = V_CE_STEP * 8 * 2;
+    struct KSet { uint4 k[A ? 1 : KC]; };
+    struct VSet { uint4 v[A ? 1 : VU][2]; };
+    int kj[KC];
+    bool vj_hi = false, vj_lo = false;
+    if constexpr (PAGED && !A) {
+      const bool slots = kvt.ps_shift < 6;
+#pragma unroll
+      for (int i = 0; i < KC; ++i)
+        kj[i] = slots ? (((wave - 4) * 64 + i * ST) / (C / 8)) >> kvt.ps_shift : 0;
+      const int v_slot = slots ? (2 * v_j) >> kvt.ps_shift : 0;
+      vj_hi = (v_slot & 2) != 0;
+      vj_lo = (v_slot & 1) != 0;
+    }
+    auto load_k = [&](const PageBases at, KSet& sk) INLINE {
+      if constexpr (!A) {
+        if constexpr (PAGED) {
+          const int vb = page_lanes(at);
+#pragma unroll
+          for (int i = 0; i < KC; ++i)
+            sk.k[i] = bload16(krs, ((uint32_t)__builtin_amdgcn_readlane(vb, kj[i]) + i * k_step) + k_boff);
+        } else {
+#pragma unroll
+          for (int i = 0; i < KC; ++i) sk.k[i] = bload16(krs, (at.b0 + i * k_step) + k_boff);
+        }
+      }
+    };
+    auto load_v = [&](const PageBases at, VSet& sv) INLINE {
+      if constexpr (!A) {
+        uint32_t b0 = at.b0, b1 = at.b0;
+        if constexpr (PAGED) v_pair_bases(at, vj_hi, vj_lo, 2 * v_j, b0, b1);
+        b0 += v_boff;
+        b1 += v_boff + st_bytes;
+#pragma unroll
+        for (int i = 0; i < VU; ++i) {
+          sv.v[i][0] = bload16(vrs, b0 + i * V_STEP);
+          sv.v[i][1] = bload16(vrs, b1 + i * V_STEP);
+        }
+      }
+    };
+    auto store_k = [&](bf16_t* dst, const KSet& sk, int i) INLINE {
+      if constexpr (!A)
+        *reinterpret_cast<uint4*>(dst + k_row * KROW + 8 * k_ce + i * K_ROW_STEP * KROW) = sk.k[i];
+    };
+    // V unit i: keys 2 v_j, + 1 x 8 channels, transposed into the V^T rows
+    auto store_v = [&](bf16_t* dst, const VSet& sv, int i) INLINE {
+      if constexpr (!A) {
+        const uint32_t* r0 = reinterpret_cast<const uint32_t*>(&sv.v[i][0]);
+        const uint32_t* r1 = reinterpret_cast<const uint32_t*>(&sv.v[i][1]);
+        bf16_t* col = dst + CF::K_ELEMS + 8 * (v_ce + i * V_CE_STEP) * VROW + vperm16(2 * v_j);
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+          const uint32_t lo = __builtin_amdgcn_perm(r1[e2], r0[e2], 0x05040100u);
+          const uint32_t hi2 = __builtin_amdgcn_perm(r1[e2], r0[e2], 0x07060302u);
+          *reinterpret_cast<uint32_t*>(col + (2 * e2) * VROW) = lo;
+          *reinterpret_cast<uint32_t*>(col + (2 * e2 + 1) * VROW) = hi2;
+        }
+      }
+    };
+
+    // ---- list head, first fetches, Q ----
+    int kt[4];   // tiles i .. i + 3
+    if (n_tiles > 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        kt[j] = DENSE ? j
+                      : __builtin_amdgcn_readfirstlane(uniform_load(
+                            a.cols, __builtin_amdgcn_readfirstlane(list_begin + min(j, n_tiles - 1))));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) kt[j] = j < n_tiles ? kt[j] : -1;
+    }
+    KSet sk;
+    VSet sv;
+    if (!A && n_tiles > 0) {
+      KSet k0;
+      VSet v0;
+      load_k(kvt.locate(kt[0]), k0);
+      load_v(kvt.locate(kt[0]), v0);
+      load_k(kvt.locate(kt[1]), sk);
+      load_v(kvt.locate(kt[1]), sv);
+#pragma unroll
+      for (int i = 0; i < KC; ++i) store_k(stage(0), k0, i);
+#pragma unroll
+      for (int i = 0; i < VU; ++i) store_v(stage(0), v0, i);
+    }
+    bf16x8 qf[U][NKC];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      // queries past N_q (never stored) repeat the last one: no branch
+      const int x = x0 + u;
+      const int t = min(qt * TILE + 16 * (blk0 + x % NB) + l16, n_q - 1);
+      const bf16_t* qp = a.q + q_off + (int64_t)(h * M + x / NB) * a.q_sh + (int64_t)t * a.q_st + 8 * g;
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) qf[u][kc] = as_bf16x8(ld16(qp + 32 * kc));
+    }
+    PageBases at{};   // of tile i + 3, the next one fetched
+    if (!A && n_tiles > 0) {
+#pragma unroll
+      for (int i = 0; i < KC; ++i) store_k(stage(1), sk, i);
+#pragma unroll
+      for (int i = 0; i < VU; ++i) store_v(stage(1), sv, i);
+      at = kvt.locate(kt[2]);
+      load_k(at, sk);
+      load_v(at, sv);
+      at = kvt.locate(kt[3]);
+    }
+
+    // ---- online softmax state: one query of each unit per lane ----
+    // l_run sums the lane's own keys (a quarter of the tile's); the four lanes
+    // of a query are added up at the end.
+    float m_run[U], l_run[U];
+    bool max_ok[U];
+    f32x4 acc[U][NCB];
+    f32x4 sc[U][4];     // keys 16 kb + 4 g + r of the tile
+    bf16x8 pf[U][2];    // P^T B operands, 32-key chunks
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      m_run[u] = -INFINITY;
+      l_run[u] = 0.f;
+      max_ok[u] = false;
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) acc[u][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    // PV of the tile in stage v_slot and / or QK of the tile in stage k_slot;
+    // fragments read DEPTH ahead in the order they are used, each feeding U
+    // MFMAs (two ahead where three units of 128 channels fill the registers)
+    constexpr int DEPTH = U == 3 && C == 128 ? 2 : 4;
+    auto stream = [&](auto do_pv, auto do_qk, int v_slot, int k_slot, auto&& hook) INLINE {
+      constexpr int NV = decltype(do_pv)::value ? 2 * NCB : 0;   // (cb, 32-key chunk)
+      constexpr int NK = decltype(do_qk)::value ? 4 * NKC : 0;   // (kb, 32-channel chunk)
+      constexpr int N = NV + NK;
+      const uint32_t va = v_lane + (uint32_t)(v_slot * CF::STAGE * 2);
+      const uint32_t ka = k_lane + (uint32_t)(k_slot * CF::STAGE * 2);
+      u32x4 ring[DEPTH];
+      auto issue = [&](auto jc) INLINE {
+        constexpr int j = decltype(jc)::value;
+        if constexpr (j < NV)
+          lds_read<(16 * (j % NCB) * VROW + 32 * (j / NCB)) * 2>(ring[j % DEPTH], va);
+        else
+          lds_read<(16 * ((j - NV) & 3) * KROW + 32 * ((j - NV) >> 2)) * 2>(ring[j % DEPTH], ka);
+      };
+      static_for<(DEPTH < N ? DEPTH : N)>(issue);
+      const f32x4 zero = {};
+      static_for<N>([&](auto jc) INLINE {
+        constexpr int j = decltype(jc)::value;
+        lgkm_wait<(N - 1 - j < DEPTH - 1 ? N - 1 - j : DEPTH - 1)>(ring[j % DEPTH]);
+        const bf16x8 av = __builtin_bit_cast(bf16x8, ring[j % DEPTH]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if constexpr (j < NV) {
+            acc[u][j % NCB] = mfma16x16(av, pf[u][j / NCB], acc[u][j % NCB]);
+          } else {
+            constexpr int kb = (j - NV) & 3;
+            sc[u][kb] = mfma16x16(av, qf[u][(j - NV) >> 2], (j - NV) < 4 ? zero : sc[u][kb]);
+          }
+        }
+        if constexpr (j + DEPTH < N) issue(std::integral_constant<int, j + DEPTH>{});
+        hook(jc);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    auto no_hook = [](auto) INLINE {};
+
+    // P = exp2(S c2 + moff) of unit u as B operands; this lane's sum of weights
+    auto exp_pack = [&](int u, float moff) INLINE -> float {
+      float r0 = 0.f, r1 = 0.f;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        uint32_t wd[4];
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb) {
+          const f32x4& v = sc[u][2 * c + hb];
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(v[0], c2, moff));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(v[1], c2, moff));
+          const float p2 = __builtin_amdgcn_exp2f(fmaf(v[2], c2, moff));
+          const float p3 = __builtin_amdgcn_exp2f(fmaf(v[3], c2, moff));
+          wd[2 * hb] = pack_bf16x2(p0, p1);
+          wd[2 * hb + 1] = pack_bf16x2(p2, p3);
+          r0 += p0;
+          r1 += p1;
+          r0 += p2;
+          r1 += p3;
+        }
+        pf[u][c] = as_bf16x8(make_uint4(wd[0], wd[1], wd[2], wd[3]));
+      }
+      return r0 + r1;
+    };
+    auto softmax = [&](int kt_s) INLINE {
+      const int key0 = kt_s * TILE;
+      const bool bad = (unsigned)kt_s >= (unsigned)t_kv;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q16 = qt * TILE + 16 * (blk0 + (x0 + u) % NB);   // the unit's first query
+        // keys past N_kv need no bound of their own: they lie past every
+        // query below N_q, and other queries are never stored
+        if (bad || key0 + TILE - 1 > n_c + q16) {
+          const int l = lane_now();
+          const int lim = (bad ? -TILE : n_c + q16 - key0) + (l & 15) - 4 * (l >> 4);
+#pragma unroll
+          for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sc[u][kb][r] = 16 * kb + r <= lim ? sc[u][kb][r] : -INFINITY;
+        }
+        bool done = false;
+        float rs = 0.f;
+        if (max_ok[u]) {
+          rs = exp_pack(u, -m_run[u] * c2);
+          done = !__builtin_amdgcn_ballot_w64(!(rs <= RESCALE_SUM));
+        }
+        if (!done) {
+          float x = sc[u][0][0];
+#pragma unroll
+          for (int i = 1; i < 16; ++i) x = fmaxf(x, sc[u][i / 4][i % 4]);
+          const float mx = max_lane4(x);
+          const bool grow = mx > m_run[u];
+          if (__builtin_amdgcn_ballot_w64(grow)) {
+            const float m_new = grow ? mx : m_run[u];
+            const float corr = grow ? __builtin_amdgcn_exp2f((m_run[u] - m_new) * c2) : 1.f;
+            m_run[u] = m_new;
+            l_run[u] *= corr;
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) acc[u][cb][r] *= corr;
+          }
+          max_ok[u] = !__builtin_amdgcn_ballot_w64(m_run[u] == -INFINITY);
+          rs = exp_pack(u, (m_run[u] == -INFINITY) ? 0.f : -m_run[u] * c2);
+        }
+        l_run[u] += rs;
+        // one unit at a time: interleaved, their temporaries spill
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+
+    // ---- ping-pong over three stages; tile i lives in stage i % 3 ----
+    //   phase Y_i:   A PV(i), QK(i+1)   | B V units of tile i+2, softmax(i)
+    //   phase X_i+1: A softmax(i+1)     | B PV(i), QK(i+1), K chunks of tile i+2
+    // Stage (i+2) % 3 == (i-1) % 3 is last read by B in phase X_i.  B refetches
+    // each register set (tile i+3) right after storing it.  Past the end of the
+    // list the loads read zeros and the stores fill a stage no one reads.
+    if (n_tiles > 0) {
+      __syncthreads();
+      if (A) stream(NO, YES, 0, 0, no_hook);
+      __syncthreads();
+      if (A) softmax(kt[0]);
+      else stream(NO, YES, 0, 0, no_hook);
+      __syncthreads();
+      int slot = 0;
+      for (int it = 0; it < n_tiles; ++it) {
+        const int slot1 = slot == 2 ? 0 : slot + 1;
+        const int slot2 = slot1 == 2 ? 0 : slot1 + 1;
+        bf16_t* const dst = stage(slot2);
+        auto stage_hook = [&](auto jc) INLINE {
+          constexpr int j = decltype(jc)::value;
+          if constexpr (!A) {
+            if constexpr (j >= 2 && j < 2 + 2 * KC && (j - 2) % 2 == 0) store_k(dst, sk, (j - 2) / 2);
+            if constexpr (j == 2 + 2 * KC) load_k(at, sk);
+          }
+        };
+        if (A) {
+          stream(YES, YES, slot, slot1, no_hook);
+        } else {
+#pragma unroll
+          for (int u = 0; u < VU; ++u) store_v(dst, sv, u);
+          load_v(at, sv);
+          softmax(kt[0]);
+        }
+        __syncthreads();
+        if (A) {
+          if (it + 1 < n_tiles) {
+            softmax(kt[1]);
+          } else {
+            // P is not needed any more: without this it stays live through the
+            // QK half of every stream
+#pragma unroll
+            for (int u = 0; u < U; ++u) pf[u][0] = pf[u][1] = bf16x8{};
+          }
+        } else {
+          stream(YES, YES, slot, slot1, stage_hook);
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) kt[j] = kt[j + 1];
+        kt[3] = tile_or_none(it + 4);
+        if constexpr (!A) at = kvt.locate(kt[3]);
+        slot = slot1;
+        __syncthreads();
+      }
+    }
+
+    // ---- epilogue: each unit's 16 x C block through LDS, whole rows out ----
+    constexpr int OROW = C + 8, LPR = C / 8, RPI = 64 / LPR;
+#pragma unroll
+    for (int u = 0; u < U; ++u) l_run[u] = add_lane4(l_run[u]);
+    __syncthreads();
+    const int lane = lane_now();
+    const int l16 = lane & 15, g = lane >> 4;
+    const int r0 = lane / LPR, ch = 8 * (lane % LPR);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int x = x0 + u, p = h * M + x / NB, q16 = qt * TILE + 16 * (blk0 + x % NB);
+      bf16_t* const ow = lds + x * 16 * OROW;
+      const float inv = (l_run[u] > 0.f) ? 1.f / l_run[u] : 0.f;
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        uint2 v;
+        v.x = pack_bf16x2(acc[u][cb][0] * inv, acc[u][cb][1] * inv);
+        v.y = pack_bf16x2(acc[u][cb][2] * inv, acc[u][cb][3] * inv);
+        *reinterpret_cast<uint2*>(ow + l16 * OROW + 16 * cb + 4 * g) = v;
+      }
+      bf16_t* const ob = a.o + o_off + (int64_t)p * a.o_sh;
+#pragma unroll
+      for (int i = 0; i < 16 / RPI; ++i) {
+        const int r = r0 + RPI * i;
+        const uint4 v = *reinterpret_cast<const uint4*>(ow + r * OROW + ch);
+        if (q16 + r < n_q) *reinterpret_cast<uint4*>(ob + (int64_t)(q16 + r) * a.o_st + ch) = v;
+      }
+      const int t = q16 + l16;
+      if (a.lse && g == 0 && t < n_q)
+        a.lse[lse_off + (int64_t)p * n_q + t] =
+            (l_run[u] > 0.f) ? m_run[u] * a.scale + logf(l_run[u]) : -INFINITY;
+    }
+  };
+  if (wave < 4) run(YES);
+  else run(NO);
+}
+
+template <int C, int M, int PARTS, int UA, int UB>
+hipError_t launch_m(const PrefillArgs& a, bool dense, int n_work, hipStream_t s) {
+  constexpr int stages = 3 * Cfg<C>::STAGE * 2, out = 4 * (UA + UB) * 16 * (C + 8) * 2;
+  constexpr int lds = stages > out ? stages : out;
+  static_assert(lds <= 160 * 1024, "LDS budget");
+  const bool paged = a.kv.paged != 0;
+  if (dense)
+    return paged ? launch_kernel<prefill_units_kernel<C, M, PARTS, UA, UB, true, true>>(a, n_work, 512, lds, s)
+                 : launch_kernel<prefill_units_kernel<C, M, PARTS, UA, UB, true, false>>(a, n_work, 512, lds, s);
+  return paged ? launch_kernel<prefill_units_kernel<C, M, PARTS, UA, UB, false, true>>(a, n_work, 512, lds, s)
+               : launch_kernel<prefill_units_kernel<C, M, PARTS, UA, UB, false, false>>(a, n_work, 512, lds, s);
+}
+
+}  // namespace
+
+hipError_t launch_prefill_units(const PrefillArgs& a, int head_dim, bool dense, int n_work,
+                                hipStream_t s) {
+  if (head_dim == 128 && a.m == 5) return launch_m<128, 5, 1, 3, 2>(a, dense, n_work, s);
+  if (head_dim == 64 && a.m == 3) return launch_m<64, 3, 1, 2, 1>(a, dense, n_work, s);
+  if (head_dim == 64 && a.m == 5) return launch_m<64, 5, 1, 3, 2>(a, dense, n_work, s);
+  if (head_dim == 64 && a.m == 6) return launch_m<64, 6, 2, 2, 1>(a, dense, n_work, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace bfla

@@ -1,0 +1,96 @@
+"""The unit prefill (GQA 5; GQA 3 and 6 at head dim 64) against float64
+attention over the same lists: lists of 0 to 7 tiles (its pipeline is three
+tiles deep), query counts around its 16-query blocks and 32-query halves,
+chunks, paged K/V, and scores that grow along a row (the running max moves)."""
+import pytest
+import torch
+
+from paper_2605_12193_amd import bfla
+from parity_util import MAX_ABS, REL_L2
+
+pytestmark = pytest.mark.gpu
+
+
+def _ref(q, k, v, rows, m, n_c, scale):
+    """q [H_q, n_q, C] in float64; rows[h][qt]: kept tiles."""
+    h_q, n_q, _ = q.shape
+    n_kv = k.shape[1]
+    o = torch.zeros(q.shape, dtype=torch.float64, device=q.device)
+    lse = torch.full((h_q, n_q), float("-inf"), dtype=torch.float64, device=q.device)
+    key = torch.arange(n_kv, device=q.device)
+    for h in range(k.shape[0]):
+        for qt, tiles in enumerate(rows[h]):
+            if not tiles:
+                continue
+            keep = torch.zeros(-(-n_kv // 64), dtype=torch.bool, device=q.device)
+            keep[tiles] = True
+            lo, hi = 64 * qt, min(64 * qt + 64, n_q)
+            ok = keep[key // 64][None] & (key[None] <= n_c + torch.arange(lo, hi, device=q.device)[:, None])
+            for p in range(m * h, m * h + m):
+                s = (q[p, lo:hi] @ k[h].t() * scale).masked_fill(~ok, float("-inf"))
+                l = torch.logsumexp(s, 1)
+                lse[p, lo:hi] = l
+                o[p, lo:hi] = torch.where(torch.isinf(l)[:, None], 0.0,
+                                          torch.exp(s - torch.where(torch.isinf(l), 0.0, l)[:, None])) @ v[h]
+    return o, lse
+
+
+@pytest.mark.parametrize("c,m", [(128, 5), (64, 3), (64, 5), (64, 6)])
+@pytest.mark.parametrize("n_q,n_kv,page,grow", [(1, 1, 0, 0), (15, 80, 16, 0), (17, 17, 0, 0),
+                                                (33, 500, 32, 0), (64, 64, 0, 0), (449, 449, 16, 0),
+                                                (449, 449, 0, 1), (700, 900, 128, 1)])
+def test_units_against_float64(c, m, n_q, n_kv, page, grow):
+    h_kv, n_c = 2, n_kv - n_q
+    gen = torch.Generator(device="cuda").manual_seed(c * m + n_q)
+    mk = lambda h, n: torch.randn(h, n, c, device="cuda", generator=gen)
+    q, k, v = mk(m * h_kv, n_q), mk(h_kv, n_kv), mk(h_kv, n_kv)
+    if grow:   # logits of about -20 to 20, rising with the key position
+        d = torch.randn(c, device="cuda", generator=gen)
+        q += 2.0 * d / d.norm() * c ** 0.25
+        k += (torch.linspace(-10, 10, n_kv, device="cuda")[:, None] * d / d.norm() * c ** 0.25)
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    t_q = -(-n_q // 64)
+    rows, flat = [], []
+    for h in range(h_kv):
+        rows.append([])
+        for qt in range(t_q):
+            causal = min(n_c + 64 * qt + 63, n_kv - 1) // 64 + 1
+            n = min((qt + h) % 8 if t_q > 1 else 8, causal)
+            pick = torch.randperm(causal, device="cuda", generator=gen)[:n].sort().values.tolist()
+            rows[h].append(pick)
+            flat += pick
+    lens = [len(r) for h in rows for r in h]
+    ptr = torch.tensor([0] + lens).cumsum(0).int().cuda()
+    cols = torch.tensor(flat + [0], dtype=torch.int32).cuda()
+    prob, prm = bfla.Problem([n_q], [n_kv], m * h_kv, h_kv, c), bfla.params()
+    if page:
+        n_p = -(-n_kv // page)
+        table = torch.randperm(n_p, device="cuda", generator=gen).int()[None].contiguous()
+        pools = []
+        for x in (k, v):
+            pad = torch.full((n_p * page, h_kv, c), 3.0, device="cuda", dtype=torch.bfloat16)
+            pad[:n_kv] = x.transpose(0, 1)
+            pool = torch.empty(n_p, page, h_kv, c, device="cuda", dtype=torch.bfloat16)
+            pool[table[0].long()] = pad.view(n_p, page, h_kv, c)
+            pools.append(pool)
+        kv = bfla.KV(*pools, paged=True, block_table=table)
+    else:
+        kv = bfla.KV(k, v)
+    qd, kd, vd = q.double(), k.double(), v.double()
+    full = [[list(range(min(n_c + 64 * qt + 63, n_kv - 1) // 64 + 1)) for qt in range(t_q)]] * h_kv
+    for dense in (False, True):
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((m * h_kv, n_q), float("nan"), device="cuda")
+        if dense:
+            bfla.bfla_dense_prefill(prob, prm, bfla.view_hnc(q), kv, bfla.view_hnc(o), lse)
+        else:
+            bfla.bfla_sparse_prefill(prob, prm, bfla.view_hnc(q), kv, ptr, cols, bfla.view_hnc(o), lse)
+        torch.cuda.synchronize()
+        wo, wl = _ref(qd, kd, vd, full if dense else rows, m, n_c, c ** -0.5)
+        err = (o.double() - wo)
+        assert err.abs().max().item() <= MAX_ABS
+        assert err.norm().item() <= REL_L2 * max(wo.norm().item(), 1e-30)
+        fin = ~torch.isinf(wl)
+        assert torch.equal(torch.isinf(lse), torch.isinf(wl))
+        # logits of up to 40 in float32, summed over 900 keys at most
+        assert (lse.double() - wl)[fin].abs().max().item() <= 2e-5 if fin.any() else True
