@@ -75,16 +75,22 @@ def parse():
     return ap.parse_args()
 
 
-PREFILL_SOURCES = ("paper_2605_12193_amd/csrc/prefill.hip", "paper_2605_12193_amd/csrc/bfla_device.h")
 SCORES_SOURCES = ("paper_2605_12193_amd/csrc/estimate.hip", "paper_2605_12193_amd/csrc/bfla_device.h")
 
 
-def prefill_source_hash(files=PREFILL_SOURCES) -> str:
-    """Hash of a kernel's code (by default prefill.hip and the device header)
+def prefill_sources():
+    """The prefill kernels' sources and headers, relative to the root."""
+    src = "paper_2605_12193_amd/csrc"
+    names = sorted(n for n in os.listdir(os.path.join(ROOT, src)) if n.startswith("prefill"))
+    return [src + "/" + n for n in names + ["bfla_device.h"]]
+
+
+def prefill_source_hash(files=None) -> str:
+    """Hash of a kernel's code (by default the prefill kernels and their headers)
     with comments and whitespace removed, so only code changes invalidate a
     committed traffic profile."""
     m = hashlib.sha256()
-    for f in files:
+    for f in files or prefill_sources():
         with open(os.path.join(ROOT, f)) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
@@ -452,7 +458,9 @@ def prefill_roofline(wl, kept, pre_ms, traffic):
     m = wl.h_q // wl.h_kv
     flop_kept = 4.0 * wl.tile * wl.tile * wl.head_dim * m * kept
     achieved = flop_kept / (pre_ms * 1e-3) / 1e12
-    return {"bound": "mfma", "kernel": "prefill_kernel (sparse)" if wl.head_dim <= 128
+    units = (wl.head_dim, m) in ((128, 5), (64, 3), (64, 5), (64, 6))
+    return {"bound": "mfma", "kernel": "prefill_units_kernel (sparse)" if units
+            else "prefill_kernel (sparse)" if wl.head_dim <= 128
             else "prefill_q16_kernel (sparse)",
             "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),

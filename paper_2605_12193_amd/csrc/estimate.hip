@@ -39,7 +39,7 @@
 namespace bfla {
 namespace {
 
-constexpr int BM = kScoreTileM;   // query groups per tile (32 per wave)
+constexpr int BM = kScoreTileM;   // rows per tile (units of 32 query groups)
 constexpr int BN = kScoreTileN;   // key groups per tile
 constexpr int BK = kScoreChunk;   // inner elements per stage
 // 8 waves (two per SIMD), 64 x 64 outputs each: four LDS fragments feed four

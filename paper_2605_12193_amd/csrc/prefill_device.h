@@ -233,7 +233,7 @@ __device__ __forceinline__ void lgkm_wait(u32x4& r) {
 // length, so they start and end together): the 128K 32/8-head layer (rho 0.1)
 // hits L2 on 66 % of its requests instead of 22 % and runs in 22.9 ms a pass
 // instead of 23.8, 32K 1.286 instead of 1.315 ms, 64K with C = 256 4.53
-// instead of 4.70 ms (one box, both sides alternating).
+// instead of 4.70 ms (one GPU, both sides alternating).
 //
 // Each wave finds its row by itself, without a workspace: lane l of the band
 // reads the list bounds of its l-th row, and the idx-th longest (equal
